@@ -825,9 +825,15 @@ __global__ __launch_bounds__(kWave * WPB) void k_dequant_reduce(
                     w[4 * k + 2] = in.c[j][k].z;
                     w[4 * k + 3] = in.c[j][k].w;
                 }
+                if constexpr (BITS_IN == 4) {
 #pragma unroll
-                for (int i = 0; i < E; ++i)
-                    acc[i] = __builtin_fmaf(code_f<BITS_IN>(w, i), in.s[j], acc[i]);
+                    for (int k = 0; k < E / 8; ++k)
+                        fma_codes4(w[k], in.s[j], acc + 8 * k);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < E; ++i)
+                        acc[i] = __builtin_fmaf(code_f<BITS_IN>(w, i), in.s[j], acc[i]);
+                }
             }
         }
         if constexpr (BITS_OUT == 0) {
