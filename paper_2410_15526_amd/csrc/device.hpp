@@ -31,13 +31,7 @@ namespace sdp4 {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-#ifndef SDP4_WAVES_PER_BLOCK
-#define SDP4_WAVES_PER_BLOCK 4
-#endif
-
 constexpr int kWave = 64;
-constexpr int kWavesPerBlock = SDP4_WAVES_PER_BLOCK; // independent wavefronts per block
-constexpr int kBlockThreads = kWave * kWavesPerBlock;
 
 SDP4_DEV int lane_id() { return __lane_id(); }
 
@@ -76,11 +70,6 @@ SDP4_DEV float xor_lane(float v)
 // row_ror:8 (lane ^ 8 within 16 lanes).  Every source lane is valid, so no
 // lane falls back to the `old` operand.
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppRor8 = 0x128;
-
-// s_waitcnt immediate (gfx9 encoding: vmcnt bits 3:0 and 15:14, expcnt 6:4,
-// lgkmcnt 11:8) that waits for every outstanding vector-memory load and
-// for nothing else.
-constexpr int kWaitVmcnt0 = 0x0F70;
 
 template <int CTRL>
 SDP4_DEV uint32_t dpp_u32(uint32_t v)
@@ -151,29 +140,6 @@ SDP4_DEV int swz_in(int c)
     return c ^ ((c >> 4) & (R - 1));
 }
 
-// Coalesced global loads of one tile: instruction i, lane l reads chunk
-// 64*i + l.  Chunks at or beyond `valid` are not read and are zero.
-// WHOLE_FAST: a whole tile (every tile but the last) is loaded without
-// per-chunk guards.  Callers that batch the loads of several buffers (the
-// peers of a dequantize-reduce) keep the guarded form, whose loads the
-// compiler schedules together.
-template <int R, bool WHOLE_FAST = true>
-SDP4_DEV void gload(const u32x4 *__restrict__ g, int valid, u32x4 (&t)[R])
-{
-    const int lane = lane_id();
-    if (WHOLE_FAST && valid >= kWave * R) {
-#pragma unroll
-        for (int i = 0; i < R; ++i)
-            t[i] = __builtin_nontemporal_load(g + kWave * i + lane);
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-        const int c = kWave * i + lane;
-        t[i] = c < valid ? __builtin_nontemporal_load(g + c) : u32x4{0u, 0u, 0u, 0u};
-    }
-}
-
 // Coalesced chunks -> lane-contiguous chunks through the wave's LDS region:
 // lane l gets the chunks R*el .. R*el+R-1 of element lane el (el = l unless
 // the kernel relabels its lanes, see element_lane).
@@ -189,78 +155,6 @@ SDP4_DEV void transpose_in(const u32x4 (&t)[R], u32x4 *lds, u32x4 (&out)[R], int
     for (int k = 0; k < R; ++k)
         out[k] = lds[swz_in<R>(R * el + k)];
     wave_lds_sync();
-}
-
-template <int R>
-SDP4_DEV void transpose_in(const u32x4 (&t)[R], u32x4 *lds, u32x4 (&out)[R])
-{
-    transpose_in<R>(t, lds, out, lane_id());
-}
-
-// The same through an LDS region of half the tile (32*R chunks): lanes
-// 0..31 take their chunks from the first half of the coalesced chunks,
-// lanes 32..63 from the second, one half after the other.
-template <int R>
-SDP4_DEV void transpose_in_halves(const u32x4 (&t)[R], u32x4 *lds, u32x4 (&out)[R])
-{
-    static_assert(R % 2 == 0, "halves");
-    const int lane = lane_id();
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-#pragma unroll
-        for (int i = 0; i < R / 2; ++i)
-            lds[swz_in<R>(kWave * i + lane)] = t[h * (R / 2) + i];
-        wave_lds_sync();
-        if ((lane >> 5) == h) {
-#pragma unroll
-            for (int k = 0; k < R; ++k)
-                out[k] = lds[swz_in<R>(R * (lane & 31) + k)];
-        }
-        wave_lds_sync();
-    }
-}
-
-// Global (coalesced) -> registers (lane-contiguous).
-template <int R>
-SDP4_DEV void stage_in(const u32x4 *__restrict__ g, int valid, u32x4 *lds, u32x4 (&out)[R])
-{
-    u32x4 t[R];
-    gload<R>(g, valid, t);
-    transpose_in<R>(t, lds, out);
-}
-
-// Registers (lane-contiguous, element lane el) -> global (coalesced).
-// Chunks at or beyond `valid` are not written.
-template <int R>
-SDP4_DEV void stage_out(u32x4 *__restrict__ g, int valid, u32x4 *lds, const u32x4 (&in)[R], int el)
-{
-    const int lane = lane_id();
-#pragma unroll
-    for (int k = 0; k < R; ++k)
-        lds[swz<R>(R * el + k)] = in[k];
-    wave_lds_sync();
-    if (valid >= kWave * R) {
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const int c = kWave * i + lane;
-            __builtin_nontemporal_store(lds[swz<R>(c)], g + c);
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const int c = kWave * i + lane;
-            const u32x4 t = lds[swz<R>(c)];
-            if (c < valid)
-                __builtin_nontemporal_store(t, g + c);
-        }
-    }
-    wave_lds_sync();
-}
-
-template <int R>
-SDP4_DEV void stage_out(u32x4 *__restrict__ g, int valid, u32x4 *lds, const u32x4 (&in)[R])
-{
-    stage_out<R>(g, valid, lds, in, lane_id());
 }
 
 template <int E>
@@ -480,10 +374,6 @@ SDP4_DEV void fwht_lane_signed(float (&v)[E], float cn, int el)
         v[i] = __builtin_fmaf(v[i], c, 0.0f);
 }
 
-// log2 of a group size (a power of two, checked on the host): header indices
-// are shifts instead of runtime 64-bit divisions.
-SDP4_DEV int group_shift(int group) { return __builtin_ctz((unsigned)group); }
-
 // ---------------------------------------------------------------------------
 // quantize and pack
 // ---------------------------------------------------------------------------
@@ -520,35 +410,12 @@ SDP4_DEV uint32_t pack_bytes4(uint32_t t0, uint32_t t1, uint32_t t2, uint32_t t3
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
-// E code words -> E bytes (int8) as E/16 chunks
-template <int E>
-SDP4_DEV void pack8(const uint32_t (&t)[E], u32x4 (&c)[E / 16])
-{
-#pragma unroll
-    for (int k = 0; k < E / 16; ++k) {
-        const uint32_t *p = t + 16 * k;
-        c[k] = u32x4{pack_bytes4(p[0], p[1], p[2], p[3]), pack_bytes4(p[4], p[5], p[6], p[7]),
-                     pack_bytes4(p[8], p[9], p[10], p[11]), pack_bytes4(p[12], p[13], p[14], p[15])};
-    }
-}
-
 // 8 code words -> 8 nibbles, element 0 in the lowest nibble
 SDP4_DEV uint32_t pack_nibbles8(const uint32_t *p)
 {
     const uint32_t ev = pack_bytes4(p[0], p[2], p[4], p[6]);
     const uint32_t od = pack_bytes4(p[1], p[3], p[5], p[7]);
     return (ev & 0x0F0F0F0Fu) | ((od << 4) & 0xF0F0F0F0u);
-}
-
-// E code words -> E/2 bytes (nibbles, even element low) as E/32 chunks
-template <int E>
-SDP4_DEV void pack4(const uint32_t (&t)[E], u32x4 (&c)[E / 32])
-{
-#pragma unroll
-    for (int k = 0; k < E / 32; ++k) {
-        const uint32_t *p = t + 32 * k;
-        c[k] = u32x4{pack_nibbles8(p), pack_nibbles8(p + 8), pack_nibbles8(p + 16), pack_nibbles8(p + 24)};
-    }
 }
 
 // ---------------------------------------------------------------------------

@@ -2,28 +2,15 @@
 // 8-bit re-quantization (K2), and of the float32 reduction and the copy.
 #include "kernels.hpp"
 
-#ifndef SDP4_COPY_BPC
-#define SDP4_COPY_BPC -64 // block cap of the copy yardstick (one block per 4 KiB chunk)
-#endif
-#ifndef SDP4_COPY_U
-#define SDP4_COPY_U 1 // 16-byte chunks per lane and block-iteration of the copy yardstick
-#endif
-#ifndef SDP4_REDF_BPC
-#define SDP4_REDF_BPC -64 // ... of the standalone float32 reduction
-#endif
-#ifndef SDP4_STREAM_BPC
-#define SDP4_STREAM_BPC 1 // ... of the read-only yardstick (persistent: one atomic per wave at the end)
-#endif
-#ifndef SDP4_FILL_BPC
-#define SDP4_FILL_BPC -64 // ... of the write-only yardstick (one block per 4 KiB)
-#endif
-
 namespace sdp4 {
 
 // ---------------------------------------------------------------------------
 // standalone float32 reduction and plain copy (16 bytes per lane per step)
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlockThreads) void k_reduce_f32(F32Table xs, int P, int64_t n,
+constexpr int kStreamWaves = 4;
+constexpr int kStreamThreads = kWave * kStreamWaves;
+
+__global__ __launch_bounds__(kStreamThreads) void k_reduce_f32(F32Table xs, int P, int64_t n,
                                                                float *__restrict__ y)
 {
     const int64_t n4 = n / 4;
@@ -51,13 +38,13 @@ __global__ __launch_bounds__(kBlockThreads) void k_reduce_f32(F32Table xs, int P
 
 // Block-contiguous copy: each block moves U * 4 KiB per iteration with U
 // 16-byte loads per lane in flight.
-constexpr int kCopyU = SDP4_COPY_U;
-__global__ __launch_bounds__(kBlockThreads) void k_copy_f32(const float *__restrict__ x,
+constexpr int kCopyU = 1;
+__global__ __launch_bounds__(kStreamThreads) void k_copy_f32(const float *__restrict__ x,
                                                              float *__restrict__ y, int64_t n)
 {
     constexpr int U = kCopyU;
     const int64_t n4 = n / 4;
-    const int64_t chunk = (int64_t)kBlockThreads * U;
+    const int64_t chunk = (int64_t)kStreamThreads * U;
     const int64_t nchunks = n4 / chunk;
     const u32x4 *xv = reinterpret_cast<const u32x4 *>(x);
     u32x4 *yv = reinterpret_cast<u32x4 *>(y);
@@ -65,10 +52,10 @@ __global__ __launch_bounds__(kBlockThreads) void k_copy_f32(const float *__restr
         u32x4 v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            v[u] = __builtin_nontemporal_load(xv + c * chunk + u * kBlockThreads + threadIdx.x);
+            v[u] = __builtin_nontemporal_load(xv + c * chunk + u * kStreamThreads + threadIdx.x);
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            __builtin_nontemporal_store(v[u], yv + c * chunk + u * kBlockThreads + threadIdx.x);
+            __builtin_nontemporal_store(v[u], yv + c * chunk + u * kStreamThreads + threadIdx.x);
     }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = nchunks * chunk * 4 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
@@ -82,8 +69,6 @@ __global__ __launch_bounds__(kBlockThreads) void k_copy_f32(const float *__restr
 // 1-KiB instructions), writes 1 KiB per wave and iteration, the grid's waves
 // interleaved so that the whole grid sweeps memory front to back.
 // ---------------------------------------------------------------------------
-constexpr int kStreamWaves = 4;
-
 // sink[k] ^= XOR of the bit patterns of x[i] over every i = k (mod 4).
 __global__ __launch_bounds__(kWave * kStreamWaves) void k_read_f32(const float *__restrict__ x, int64_t n,
                                                                    uint32_t *__restrict__ sink)
@@ -149,48 +134,39 @@ int launch_dequant_reduce(const PeerTable &peers, int P, int64_t n, int bits_in,
         return bits_in == 8
                    ? launch_dequant_reduce_f32_in8(peers, P, n, group, nblk, cn, out_scale, out_f32, s)
                    : launch_dequant_reduce_f32_in4(peers, P, n, group, nblk, cn, out_scale, out_f32, s);
-    const bool wide = use_wide_lanes(group, SDP4_E_RED);
-    if (bits_in == 8 && SDP4_E_RQ8 == 16 && group <= kWave * 16) { // a group must fit one wavefront
-        if (bits_out == 4)
-            return dr_launch<8, 4, 16, 0>(peers, P, n, group, cn, 1.0f, out_codes, out_scales, out_f32, s);
-        return dr_launch<8, 8, 16, 0>(peers, P, n, group, cn, 1.0f, out_codes, out_scales, out_f32, s);
-    }
-    if (bits_in == 8) {
-        if (bits_out == 4)
-            return wide ? dr_launch<8, 4, 64, 0>(peers, P, n, group, cn, 1.0f, out_codes, out_scales, out_f32, s)
-                        : dr_launch<8, 4, 32, 0>(peers, P, n, group, cn, 1.0f, out_codes, out_scales, out_f32, s);
-        return wide ? dr_launch<8, 8, 64, 0>(peers, P, n, group, cn, 1.0f, out_codes, out_scales, out_f32, s)
-                    : dr_launch<8, 8, 32, 0>(peers, P, n, group, cn, 1.0f, out_codes, out_scales, out_f32, s);
-    }
-    if (bits_out == 4)
-        return wide ? dr_launch<4, 4, 64, 0>(peers, P, n, group, cn, 1.0f, out_codes, out_scales, out_f32, s)
-                    : dr_launch<4, 4, 32, 0>(peers, P, n, group, cn, 1.0f, out_codes, out_scales, out_f32, s);
-    return wide ? dr_launch<4, 8, 64, 0>(peers, P, n, group, cn, 1.0f, out_codes, out_scales, out_f32, s)
-                : dr_launch<4, 8, 32, 0>(peers, P, n, group, cn, 1.0f, out_codes, out_scales, out_f32, s);
+    const int gs = log2_of(group);
+    if (bits_in == 8)
+        return bits_out == 4 ? requant_any<8, 4, false>(peers, P, n, gs, out_codes, out_scales, out_f32, s, 0, 0)
+                             : requant_any<8, 8, false>(peers, P, n, gs, out_codes, out_scales, out_f32, s, 0, 0);
+    return bits_out == 4 ? requant_any<4, 4, false>(peers, P, n, gs, out_codes, out_scales, out_f32, s, 0, 0)
+                         : requant_any<4, 8, false>(peers, P, n, gs, out_codes, out_scales, out_f32, s, 0, 0);
 }
+
+// Blocks of a kernel that loops with the stride of a one-dimensional grid.
+static int64_t looped(int64_t blocks) { return blocks < kGridX ? blocks : kGridX; }
 
 int launch_reduce_f32(const F32Table &xs, int P, int64_t n, float *y, hipStream_t s)
 {
-    const int64_t blocks = (n / 4 + kBlockThreads - 1) / kBlockThreads;
-    return launch<kWavesPerBlock>(k_reduce_f32, blocks > 0 ? blocks : 1, SDP4_REDF_BPC, s, xs, P, n, y);
+    const int64_t blocks = (n / 4 + kStreamThreads - 1) / kStreamThreads;
+    return launch<kStreamWaves>(k_reduce_f32, looped(blocks), kUncapped, s, xs, P, n, y);
 }
 
 int launch_read_f32(const float *x, int64_t n, uint32_t *sink, hipStream_t s)
 {
     const int64_t tiles = n / (4 * kWave * 8);
-    return launch<kStreamWaves>(k_read_f32, tiles > 0 ? tiles : 1, SDP4_STREAM_BPC, s, x, n, sink);
+    return launch<kStreamWaves>(k_read_f32, looped(tiles), kPersistent, s, x, n, sink);
 }
 
 int launch_fill_f32(float *y, int64_t n, float value, hipStream_t s)
 {
     const int64_t blocks = n / 4 / (kWave * kStreamWaves);
-    return launch<kStreamWaves>(k_fill_f32, blocks > 0 ? blocks : 1, SDP4_FILL_BPC, s, y, n, value);
+    return launch<kStreamWaves>(k_fill_f32, looped(blocks), kUncapped, s, y, n, value);
 }
 
 int launch_copy_f32(const float *x, float *y, int64_t n, hipStream_t s)
 {
-    const int64_t chunks = n / 4 / (kBlockThreads * kCopyU);
-    return launch<kWavesPerBlock>(k_copy_f32, chunks > 0 ? chunks : 1, SDP4_COPY_BPC, s, x, y, n);
+    const int64_t chunks = n / 4 / (kStreamThreads * kCopyU);
+    return launch<kStreamWaves>(k_copy_f32, looped(chunks), kUncapped, s, x, y, n);
 }
 
 } // namespace sdp4

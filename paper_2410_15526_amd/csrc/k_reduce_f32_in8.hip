@@ -11,11 +11,7 @@ struct DequantReduceF32 {
     static int run(const PeerTable &peers, int P, int64_t n, int group, float cn, float out_scale,
                    float *out_f32, hipStream_t s)
     {
-        if (use_wide_lanes(group, SDP4_E_RED))
-            return dr_launch<8, 0, 64, NB>(peers, P, n, group, cn, out_scale, nullptr, nullptr, out_f32, s);
-        if constexpr (SDP4_E_RF8 == 16 && NB <= kWave * 16)
-            return dr_launch<8, 0, 16, NB>(peers, P, n, group, cn, out_scale, nullptr, nullptr, out_f32, s);
-        return dr_launch<8, 0, 32, NB>(peers, P, n, group, cn, out_scale, nullptr, nullptr, out_f32, s);
+        return reduce_to_f32<8, NB>(peers, P, n, log2_of(group), cn, out_scale, out_f32, s);
     }
 };
 

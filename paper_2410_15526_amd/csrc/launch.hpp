@@ -23,38 +23,39 @@ struct F32Table {
 // Records `err` as the calling thread's last HIP error and returns SDP4_EHIP.
 int set_hip_error(hipError_t err);
 
-// per_cu_cap values that ask for one block per work block (up to kMaxGrid):
-// the hardware dispatches blocks in index order, so the chip's accesses sweep
-// memory from front to back, which HBM serves faster than the scattered
-// fronts of a persistent grid (every kernel loops over its tiles, so any
-// grid size computes the same result).  kFullGrid leaves residency to the
-// kernel's occupancy; -k (1 <= k < 64) also reserves enough LDS per block
-// that at most k blocks are resident on a compute unit at once.
-constexpr int kFullGrid = -64;
-constexpr int64_t kMaxGrid = 0x7FFFFFFF;
+// Grids.  A launch has one block per work block: the hardware dispatches
+// blocks in index order, so the chip's accesses sweep memory from front to
+// back, which HBM serves faster than the scattered fronts of a persistent
+// grid.  `cap` bounds the blocks resident on a compute unit at once: k >= 1
+// reserves enough LDS per block that at most k fit, kUncapped leaves residency
+// to the kernel's occupancy.  kPersistent: as many blocks as compute units
+// (the kernel loops over its work blocks).
+constexpr int kUncapped = 0;
+constexpr int kPersistent = -1;
+
+// Launches of up to this many blocks per compute unit take no cap: they are
+// over in a round or two, and have no steady state for a cap to pace.  (us
+// with the cap / without: 2^22 elements, 4 to 8 blocks per CU, encode 6.4 / 5.8,
+// decode of float32 weights at 2^21 4.6 / 4.1, 2^23 elements, encode 10.2 / 9.8,
+// K1 4-bit 8.1 / 7.8; from 12 blocks on the caps are as fast or faster.)
+constexpr int kPacedBlocks = 10;
+
+// Blocks along x; the rest go along y, since the work items of one dimension
+// must stay below 2^32.  Block (x, y) is work block y * kGridX + x.
+constexpr int64_t kGridXLog2 = 22, kGridX = int64_t(1) << kGridXLog2;
 
 struct LaunchShape {
-    int grid;
+    unsigned x, y;
     size_t dyn_lds; // LDS bytes reserved per block beyond the kernel's own
 };
-
-// Grid of a kernel that loops over its work blocks: with per_cu_cap < 0 one
-// block per work block (see kFullGrid); otherwise a persistent grid of the
-// blocks of `kernel` (block_threads threads each) that are resident at once
-// on the current device (capped at per_cu_cap per compute unit when
-// per_cu_cap > 0), and never more than nwork_blocks.
-LaunchShape shape_for(const void *kernel, int64_t nwork_blocks, int per_cu_cap, int block_threads, hipError_t &err);
-int grid_for(const void *kernel, int64_t nwork_blocks, int per_cu_cap, int block_threads, hipError_t &err);
-
-// Rate of the device's constant wall clock in kHz (cached per device).
-int wall_clock_khz(hipError_t &err);
+LaunchShape shape_for(const void *kernel, int64_t nwork_blocks, int cap, hipError_t &err);
 
 // Launch `kernel` with blocks of WAVES wavefronts.
 template <int WAVES, typename... Params, typename... Args>
-int launch(void (*kernel)(Params...), int64_t nwork_blocks, int per_cu_cap, hipStream_t stream, Args... args)
+int launch(void (*kernel)(Params...), int64_t nwork_blocks, int cap, hipStream_t stream, Args... args)
 {
     hipError_t err;
-    const LaunchShape sh = shape_for(reinterpret_cast<const void *>(kernel), nwork_blocks, per_cu_cap, 64 * WAVES, err);
+    const LaunchShape sh = shape_for(reinterpret_cast<const void *>(kernel), nwork_blocks, cap, err);
     if (err != hipSuccess)
         return set_hip_error(err);
     std::tuple<Params...> values(args...);
@@ -63,8 +64,8 @@ int launch(void (*kernel)(Params...), int64_t nwork_blocks, int per_cu_cap, hipS
         int i = 0;
         ((argv[i++] = static_cast<void *>(&v)), ...);
     }, values);
-    err = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(sh.grid), dim3(64 * WAVES), argv, sh.dyn_lds,
-                          stream);
+    err = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(sh.x, sh.y), dim3(64 * WAVES), argv,
+                          sh.dyn_lds, stream);
     if (err != hipSuccess)
         return set_hip_error(err);
     return 0;

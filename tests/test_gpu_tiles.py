@@ -30,3 +30,131 @@ def test_every_nibble_at_every_position_with_extreme_scales(P):
     sync()
     ref = oracle.dequant_reduce([c for c, _ in msgs], [s for _, s in msgs], n, 4, group, 0, 0, 1.0)
     check_f32(host(out), ref["f32"])
+
+
+def _weights(n, bf16, seed):
+    rng = np.random.default_rng(seed)
+    prev = rng.standard_normal(n, dtype=np.float32) * np.float32(0.02)
+    if bf16:
+        prev = oracle.bf16_rne(prev)
+    wide = oracle.bf16_to_f32(prev) if bf16 else prev
+    return wide + rng.standard_normal(n, dtype=np.float32) * np.float32(5e-4), prev
+
+
+# One group, one block (2048 and 4096 elements), one group less or more, and
+# several blocks with a partial last one; groups inside a wave tile (512, 1024
+# elements), over it, and as large as a block.
+SIZES = [(32, 32), (32, 2048 - 32), (32, 4096 + 32), (512, 4096 - 512), (512, 3 * 4096 + 512), (1024, 1024),
+         (1024, 5 * 4096 - 1024), (2048, 2048), (2048, 4096), (2048, 3 * 4096 + 2048), (4096, 4096), (4096, 5 * 4096)]
+
+
+@pytest.mark.parametrize("group,n", SIZES)
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("sym", [False, True])
+def test_qwd_at_block_edges(group, n, bf16, sym):
+    say(f"qwd edges group={group} n={n} bf16={bf16} sym={sym}")
+    new, prev = _weights(n, bf16, n + group)
+    pd = dev(prev)
+    codes, scale, minv = empty(n // 2, "u8"), empty(n // group, "f32"), empty(n // group, "f32")
+    if sym:
+        sdp4.sdp4_qwd_encode_sym(dev(new), pd, group, codes, scale)
+        want = oracle.qwd_encode_sym(new, prev, group)
+        sdp4.sdp4_qwd_decode_sym(codes, scale, group, pd)
+        after = oracle.qwd_decode_sym(want[0], want[1], prev, group)
+    else:
+        sdp4.sdp4_qwd_encode(dev(new), pd, group, codes, scale, minv)
+        want = oracle.qwd_encode(new, prev, group)
+        sdp4.sdp4_qwd_decode(codes, scale, minv, group, pd)
+        after = oracle.qwd_decode(want[0], want[1], want[2], prev, group)
+        assert np.array_equal(host(minv), want[2])
+    sync()
+    assert np.array_equal(host(codes), want[0]) and np.array_equal(host(scale), want[1])
+    assert np.array_equal(host(pd), after)
+
+
+@pytest.mark.parametrize("group,n", SIZES)
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("block", [0, 32, 512])
+@pytest.mark.parametrize("sr", [False, True])
+def test_grad_quant_at_block_edges(group, n, bits, block, sr):
+    n = -(-n // max(block, 1)) * max(block, 1)
+    say(f"grad_quant edges group={group} n={n} bits={bits} block={block} sr={sr}")
+    x = np.random.default_rng(n + bits).standard_normal(n, dtype=np.float32) * np.float32(1e-4)
+    codes, scale = empty(n * bits // 8, "u8"), empty(n // group, "f32")
+    if sr:
+        sdp4.sdp4_grad_quant_sr(dev(x), bits, block, group, 77, 8, codes, scale)
+        want = oracle.grad_quant_sr(x, bits, block, group, 77, 8)
+    else:
+        sdp4.sdp4_grad_quant(dev(x), bits, block, group, codes, scale)
+        want = oracle.grad_quant(x, bits, block, group)
+    sync()
+    assert np.array_equal(host(codes), np.ascontiguousarray(want[0]).view(np.uint8))
+    assert np.array_equal(host(scale), want[1])
+
+
+def _messages(P, n, bits, group, seed):
+    rng = np.random.default_rng(seed)
+    top = 127 if bits == 8 else 7
+    out = []
+    for _ in range(P):
+        q = np.clip(np.rint(rng.standard_normal(n, dtype=np.float32) * (top / 3)), -top, top).astype(np.int8)
+        codes = q.view(np.uint8) if bits == 8 else ((q[0::2] & 15) | ((q[1::2] & 15) << 4)).astype(np.uint8)
+        out.append((codes, (np.exp(rng.standard_normal(n // group)) * 1e-5).astype(np.float32)))
+    return out
+
+
+# Every peer count with a kernel of its own and one of each guarded kernel,
+# at block edges; above 2^22 elements 4-bit messages take 32 elements per lane.
+@pytest.mark.parametrize("P", [1, 2, 3, 4, 5, 8, 11, 16])
+@pytest.mark.parametrize("bits_in", [4, 8])
+@pytest.mark.parametrize("group,n", [(32, 4096 + 32), (1024, 3 * 4096 - 1024), (2048, 8192 + 2048), (4096, 8192 + 4096)])
+def test_requant_at_block_edges(P, bits_in, group, n):
+    say(f"requant edges P={P} in={bits_in} group={group} n={n}")
+    msgs = _messages(P, n, bits_in, group, P + n)
+    cd, sd = [dev(c) for c, _ in msgs], [dev(s) for _, s in msgs]
+    for bits_out in (4, 8):
+        for seed in (None, 5):
+            oc, osc = empty(n * bits_out // 8, "u8"), empty(n // group, "f32")
+            if seed is None:
+                sdp4.sdp4_dequant_reduce(cd, sd, n, bits_in, group, bits_out, out_codes=oc, out_scales=osc)
+                ref = oracle.dequant_reduce([c for c, _ in msgs], [s for _, s in msgs], n, bits_in, group, bits_out)
+            else:
+                sdp4.sdp4_dequant_reduce_sr(cd, sd, n, bits_in, group, bits_out, seed, 16, oc, osc)
+                ref = oracle.dequant_reduce_sr([c for c, _ in msgs], [s for _, s in msgs], n, bits_in, group, bits_out,
+                                               seed, 16)
+            sync()
+            assert np.array_equal(host(oc), np.ascontiguousarray(ref["codes"]).view(np.uint8))
+            assert np.array_equal(host(osc), ref["scales"])
+
+
+@pytest.mark.parametrize("group,extra", [(128, -128), (128, 0), (128, 128), (2048, 2048), (4096, 4096)])
+def test_requant_of_4_bit_messages_around_its_lane_width_switch(group, extra):
+    P, n = 3, (1 << 22) + extra
+    say(f"requant 4-bit n={n} group={group}")
+    msgs = _messages(P, n, 4, group, n)
+    oc, osc = empty(n // 2, "u8"), empty(n // group, "f32")
+    sdp4.sdp4_dequant_reduce([dev(c) for c, _ in msgs], [dev(s) for _, s in msgs], n, 4, group, 4, out_codes=oc,
+                             out_scales=osc)
+    sync()
+    ref = oracle.dequant_reduce([c for c, _ in msgs], [s for _, s in msgs], n, 4, group, 4)
+    assert np.array_equal(host(oc), np.ascontiguousarray(ref["codes"]).view(np.uint8))
+    assert np.array_equal(host(osc), ref["scales"])
+
+
+def test_launch_of_more_blocks_than_one_grid_dimension_takes():
+    """2^22 blocks go along x: a decode of more than 2^32 float32 weights (1024
+    per block) covers a second row.  Scales, minima and weights are small whole
+    numbers, so every result is exact in float32."""
+    t = torch()
+    group, n = 4096, (1 << 32) + 5 * 4096
+    say(f"decode n={n}")
+    w = t.ones(n, dtype=t.float32, device="cuda")
+    codes = t.randint(0, 256, (n // 2,), dtype=t.uint8, device="cuda")
+    scale = t.randint(1, 8, (n // group,), device="cuda").float()
+    minv = t.randint(-8, 8, (n // group,), device="cuda").float()
+    sdp4.sdp4_qwd_decode(codes, scale, minv, group, w)
+    for a, b in ((0, 1 << 20), ((1 << 32) - (1 << 20), (1 << 32) + 4096), (n - 4096, n)):
+        c = codes[a // 2:b // 2]
+        q = t.stack((c & 15, c >> 4), 1).view(-1, group).float()
+        want = 1 + q * scale[a // group:b // group].view(-1, 1) + minv[a // group:b // group].view(-1, 1)
+        assert t.equal(w[a:b].view(-1, group), want), (a, b)
