@@ -6,24 +6,29 @@ namespace sdp4 {
 
 namespace {
 
-// 16 elements per lane in blocks of 4 waves, <= 6 per CU.
-template <int BITS, int NB>
+template <int BITS, int E, int NB, int WPB>
 int quantize_sr(const float *x, int64_t n, int gs, float cn, uint64_t seed, uint64_t offset, uint8_t *codes,
-                float *scale, hipStream_t s)
+                float *scale, int cap, hipStream_t s)
 {
-    constexpr int E = 16, WPB = 4;
     auto k = (1 << gs) > kWave * E ? k_grad_quant<BITS, E, NB, WPB, true, true>
                                    : k_grad_quant<BITS, E, NB, WPB, true, false>;
-    return launch_tiles<E, WPB>(k, n, 6, s, x, n, gs, cn, codes, scale, seed, offset);
+    return launch_tiles<E, WPB>(k, n, cap, s, x, n, gs, cn, codes, scale, seed, offset);
 }
 
+// 16 elements per lane in 4-wave blocks, <= 6 per CU, where the transform adds to the generator's work; with at
+// most 32 points and 8-bit codes HBM bounds it, and 8 per lane in 8-wave blocks are faster (2^27 elements, block
+// 0 / 32 / 128 / 256: 104.1 / 105.0 / 110.5 / 113.5 us, 16 per lane 110.2 / 109.8 / 109.1 / 106.2).
 template <int NB>
 struct GradQuantSR {
     static int run(const float *x, int64_t n, int bits, int gs, float cn, uint64_t seed, uint64_t offset,
                    uint8_t *codes, float *scale, hipStream_t s)
     {
-        return bits == 8 ? quantize_sr<8, NB>(x, n, gs, cn, seed, offset, codes, scale, s)
-                         : quantize_sr<4, NB>(x, n, gs, cn, seed, offset, codes, scale, s);
+        if (bits == 4)
+            return quantize_sr<4, 16, NB, 4>(x, n, gs, cn, seed, offset, codes, scale, 6, s);
+        if constexpr (NB <= 32)
+            return quantize_sr<8, 8, NB, 8>(x, n, gs, cn, seed, offset, codes, scale, kUncapped, s);
+        else
+            return quantize_sr<8, 16, NB, 4>(x, n, gs, cn, seed, offset, codes, scale, 6, s);
     }
 };
 

@@ -221,11 +221,11 @@ template <int E, bool SR>
 SDP4_DEV void sym_codes(const float (&v)[E], float inv, float qmax, uint64_t seed, uint64_t e0, uint32_t (&q)[E])
 {
     if constexpr (SR) {
-        float u[E];
-        sr_uniforms<E>(seed, e0, u);
+        float h[E];
+        sr_uniforms<E>(seed, e0, h);
 #pragma unroll
         for (int i = 0; i < E; ++i)
-            q[i] = code_bits_sr(v[i], inv, u[i], qmax);
+            q[i] = code_bits_sr(v[i], inv, h[i], (int)qmax);
     } else {
 #pragma unroll
         for (int i = 0; i < E; ++i)

@@ -158,3 +158,21 @@ def test_launch_of_more_blocks_than_one_grid_dimension_takes():
         q = t.stack((c & 15, c >> 4), 1).view(-1, group).float()
         want = 1 + q * scale[a // group:b // group].view(-1, 1) + minv[a // group:b // group].view(-1, 1)
         assert t.equal(w[a:b].view(-1, group), want), (a, b)
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+def test_stochastic_rounding_of_group_extremes(bits):
+    """Elements at +-(the group's largest magnitude), whose product with the
+    inverse scale can land one ulp beyond the last level, on either side."""
+    group, groups = 32, 1 << 14
+    say(f"sr extremes bits={bits}")
+    rng = np.random.default_rng(bits)
+    s = np.exp(rng.uniform(-60, 60, groups)).astype(np.float32)
+    x = (rng.choice(np.float32([-1, 1]), (groups, group)) * s[:, None]).astype(np.float32).reshape(-1)
+    codes, scale = empty(x.size * bits // 8, "u8"), empty(groups, "f32")
+    for seed in range(3):
+        sdp4.sdp4_grad_quant_sr(dev(x), bits, 0, group, seed, 0, codes, scale)
+        sync()
+        want = oracle.grad_quant_sr(x, bits, 0, group, seed, 0)
+        assert np.array_equal(host(codes), np.ascontiguousarray(want[0]).view(np.uint8))
+        assert np.array_equal(host(scale), want[1])
