@@ -2,7 +2,8 @@
 
 Usable as ``python -m paper_2410_15526_amd.build``.  Each source compiles
 to an object under ``_build/`` (in parallel), then one shared library is
-linked next to this file.
+linked next to this file, and with it ``_binding.so``, the Python binding's
+argument marshalling (a CPython extension on torch's headers).
 """
 from __future__ import annotations
 
@@ -20,6 +21,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libsdp4.so")
 SOURCES = ["k_qwd.hip", "k_grad.hip", "k_sr.hip", "k_reduce.hip", "k_reduce_f32_in8.hip", "k_reduce_f32_in4.hip",
            "launch.cpp", "abi.cpp"]
+BINDING = os.path.join(PKG, "_binding.so")
 ARCH = "gfx950"
 
 FLAGS = [
@@ -47,14 +49,38 @@ def _compile(src: str, bdir: str, defines) -> str:
     return obj
 
 
+def build_binding(out: str = BINDING) -> str:
+    """Compile ``_binding.so`` with g++ (host code only)."""
+    import sysconfig
+
+    import torch
+    troot = os.path.dirname(torch.__file__)
+    tmp = out + f".tmp{os.getpid()}"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INCLUDE,
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(troot, "include"),
+           "-isystem", os.path.join(troot, "include", "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(os.path.dirname(os.path.dirname(hipcc())), "include"),
+           os.path.join(CSRC, "binding.cpp"), "-o", tmp, "-L", os.path.join(troot, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for binding.cpp:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, out)
+    return out
+
+
 def build(verbose: bool = False, defines=(), out: str | None = None, build_dir: str | None = None) -> str:
     """Compile and link.  ``defines`` and ``out`` exist for tuning builds
     (e.g. ``defines=["SDP4_PIPE=0"]``); the default build uses neither."""
     bdir = build_dir or BUILD
     lib = out or LIB
     os.makedirs(bdir, exist_ok=True)
-    with cf.ThreadPoolExecutor(len(SOURCES)) as ex:
+    with cf.ThreadPoolExecutor(len(SOURCES) + 1) as ex:
+        binding = ex.submit(build_binding) if out is None else None
         objs = list(ex.map(lambda s: _compile(s, bdir, defines), SOURCES))
+        if binding is not None:
+            binding.result()
     tmp = lib + f".tmp{os.getpid()}"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)

@@ -107,14 +107,26 @@ class HotPath:
         return ([self.c4[q * m // 2:(q + 1) * m // 2] for q in range(self.Q)],
                 [self.s4[q * m // g:(q + 1) * m // g] for q in range(self.Q)])
 
+    # The chunks as the launches take them: addresses where the buffers are plain (slicing 16 chunk
+    # tensors takes longer than a small reduction runs), else the slices.
+    def _intra(self, bits):
+        M = self.M
+        return (sdp4.chunk_addresses(self.c8, self.s8, self.P, M * bits // 8, M // self.group)
+                or self.intra_chunks(bits))
+
+    def _inter(self):
+        m = self.m
+        return (sdp4.chunk_addresses(self.c4, self.s4, self.Q, m // 2, m // self.group)
+                or self.inter_chunks())
+
     def reduce_intra(self, stream=None, bits_in=8):
-        c, s = self.intra_chunks(bits_in)
+        c, s = self._intra(bits_in)
         sdp4.sdp4_dequant_reduce(c, s, self.M, bits_in, self.group, 4, 0, 1.0, self.c4, self.s4, None,
                                  stream=stream)
 
     def reduce_inter(self, stream=None, block=None):
         block = self.block if block is None else block
-        c, s = self.inter_chunks()
+        c, s = self._inter()
         sdp4.sdp4_dequant_reduce(c, s, self.m, 4, self.group, 0, block, self.out_scale, None, None,
                                  self.out, stream=stream)
 
@@ -127,7 +139,7 @@ class HotPath:
                                 stream=stream)
 
     def reduce_intra_sr(self, stream=None, bits_in=8):
-        c, s = self.intra_chunks(bits_in)
+        c, s = self._intra(bits_in)
         sdp4.sdp4_dequant_reduce_sr(c, s, self.M, bits_in, self.group, 4, self.SR_SEEDS[1], 0, self.c4, self.s4,
                                     stream=stream)
 

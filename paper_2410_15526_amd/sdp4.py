@@ -6,6 +6,12 @@ for the arrays, derives element counts and dtypes from tensors where the C
 call needs them, passes torch's current HIP stream unless one is given, and
 raises :class:`Sdp4Error` on a non-zero status.  No computation happens
 here, and there is no fallback: without the built library every call raises.
+
+A call's way to its launch costs more than most small kernels run, so the
+marshalling of ordinary arguments (torch tensors or addresses, plain ints,
+the current stream or a stream's address) is native, in ``_binding.so``;
+whatever that hands back as out of the ordinary takes the general path here,
+which also reports what is wrong with it.
 """
 from __future__ import annotations
 
@@ -16,6 +22,7 @@ import threading
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libsdp4.so")
 _lock = threading.Lock()
 _lib = None
+_fast = None  # the native marshalling, bound to the loaded library
 
 OK, EINVAL, EALIGN, ERANGE, EHIP = 0, 1, 2, 3, 4
 F32, BF16 = 0, 1
@@ -65,8 +72,32 @@ def lib() -> C.CDLL:
             for name, (res, args) in sig.items():
                 fn = getattr(L, name)
                 fn.restype, fn.argtypes = res, args
+            _bind(L)
             _lib = L
     return _lib
+
+
+def _bind(L) -> None:
+    """Point the native marshalling at the library's entry points."""
+    global _fast
+    try:
+        import torch  # noqa: F401  the extension's libraries come with torch
+    except ImportError:
+        return  # addresses only, on the general path
+    from . import _binding
+    _binding.bind(*[C.cast(getattr(L, "sdp4_" + n), C.c_void_p).value for n in
+                    ("qwd_encode", "qwd_decode", "qwd_encode_sym", "qwd_decode_sym", "grad_quant", "grad_quant_sr",
+                     "dequant_reduce", "dequant_reduce_sr")])
+    _fast = _binding
+
+
+def _done(name: str, rc) -> bool:
+    """Whether the native path made the call (rc None: it did not)."""
+    if rc is None:
+        return False
+    if rc != OK:
+        raise Sdp4Error(name, rc)
+    return True
 
 
 def _ptr(x):
@@ -129,6 +160,9 @@ def _ck(name: str, rc: int) -> None:
 
 def sdp4_qwd_encode(w_new, w_prev, group, codes, scale, minv, n=None, stream=None):
     """codes/scale/minv <- 4-bit quantized (w_new - w_prev); see include/sdp4.h."""
+    if _fast is not None and _done("sdp4_qwd_encode", _fast.qwd_encode(
+            w_new, w_prev, group, codes, scale, minv, n, stream)):
+        return
     n = w_new.numel() if n is None else n
     _need(w_new, 4 * n, "w_new"); _need(w_prev, _prev_bytes(w_prev, n), "w_prev"); _need(codes, n // 2, "codes")
     _need(scale, 4 * _ng(n, group), "scale"); _need(minv, 4 * _ng(n, group), "minv")
@@ -138,6 +172,8 @@ def sdp4_qwd_encode(w_new, w_prev, group, codes, scale, minv, n=None, stream=Non
 
 def sdp4_qwd_decode(codes, scale, minv, group, w_prev, n=None, stream=None):
     """w_prev <- w_prev + dequantized message, in place."""
+    if _fast is not None and _done("sdp4_qwd_decode", _fast.qwd_decode(codes, scale, minv, group, w_prev, n, stream)):
+        return
     n = w_prev.numel() if n is None else n
     _need(codes, n // 2, "codes"); _need(scale, 4 * _ng(n, group), "scale"); _need(minv, 4 * _ng(n, group), "minv")
     _need(w_prev, _prev_bytes(w_prev, n), "w_prev")
@@ -147,6 +183,9 @@ def sdp4_qwd_decode(codes, scale, minv, group, w_prev, n=None, stream=None):
 
 def sdp4_qwd_encode_sym(w_new, w_prev, group, codes, scale, n=None, stream=None):
     """codes/scale <- symmetric 4-bit quantized (w_new - w_prev); see include/sdp4.h."""
+    if _fast is not None and _done("sdp4_qwd_encode_sym", _fast.qwd_encode_sym(
+            w_new, w_prev, group, codes, scale, n, stream)):
+        return
     n = w_new.numel() if n is None else n
     _need(w_new, 4 * n, "w_new"); _need(w_prev, _prev_bytes(w_prev, n), "w_prev"); _need(codes, n // 2, "codes")
     _need(scale, 4 * _ng(n, group), "scale")
@@ -156,6 +195,8 @@ def sdp4_qwd_encode_sym(w_new, w_prev, group, codes, scale, n=None, stream=None)
 
 def sdp4_qwd_decode_sym(codes, scale, group, w_prev, n=None, stream=None):
     """w_prev <- w_prev + dequantized symmetric message, in place."""
+    if _fast is not None and _done("sdp4_qwd_decode_sym", _fast.qwd_decode_sym(codes, scale, group, w_prev, n, stream)):
+        return
     n = w_prev.numel() if n is None else n
     _need(codes, n // 2, "codes"); _need(scale, 4 * _ng(n, group), "scale"); _need(w_prev, _prev_bytes(w_prev, n), "w_prev")
     _ck("sdp4_qwd_decode_sym", lib().sdp4_qwd_decode_sym(_ptr(codes), _ptr(scale), n, group, _ptr(w_prev),
@@ -163,6 +204,9 @@ def sdp4_qwd_decode_sym(codes, scale, group, w_prev, n=None, stream=None):
 
 
 def sdp4_grad_quant(x, bits, hadamard_block, group, codes, scale, n=None, stream=None):
+    if _fast is not None and _done("sdp4_grad_quant", _fast.grad_quant(
+            x, bits, hadamard_block, group, codes, scale, n, stream)):
+        return
     n = x.numel() if n is None else n
     _need(x, 4 * n, "x"); _need(codes, n * bits // 8, "codes"); _need(scale, 4 * _ng(n, group), "scale")
     _ck("sdp4_grad_quant", lib().sdp4_grad_quant(_ptr(x), n, bits, hadamard_block, group, _ptr(codes),
@@ -182,6 +226,9 @@ def _need_reduce(codes, scales, n_chunk, bits_in, group, bits_out, out_codes, ou
 def sdp4_dequant_reduce(codes, scales, n_chunk, bits_in, group, bits_out, hadamard_block=0,
                         out_scale=1.0, out_codes=None, out_scales=None, out_f32=None, stream=None):
     """``codes``/``scales``: sequences of P chunk tensors (or addresses)."""
+    if _fast is not None and _done("sdp4_dequant_reduce", _fast.dequant_reduce(
+            codes, scales, n_chunk, bits_in, group, bits_out, hadamard_block, out_scale, out_codes, out_scales, out_f32, stream)):
+        return
     P = len(codes)
     if len(scales) != P:
         raise ValueError("sdp4_dequant_reduce: codes and scales differ in length")
@@ -194,8 +241,19 @@ def sdp4_dequant_reduce(codes, scales, n_chunk, bits_in, group, bits_out, hadama
         _stream(stream)))
 
 
+def chunk_addresses(codes, scales, count, code_bytes, headers):
+    """Device addresses of ``count`` consecutive chunks of a message (each
+    ``code_bytes`` of codes and ``headers`` group headers) as two lists for
+    sdp4_dequant_reduce, or None where the tensors are not plain device
+    buffers that hold them all."""
+    return None if _fast is None else _fast.chunk_addresses(codes, scales, count, code_bytes, headers)
+
+
 def sdp4_grad_quant_sr(x, bits, hadamard_block, group, seed, offset, codes, scale, n=None, stream=None):
     """Stochastically rounded sdp4_grad_quant (unbiased; see include/sdp4.h)."""
+    if _fast is not None and _done("sdp4_grad_quant_sr", _fast.grad_quant_sr(
+            x, bits, hadamard_block, group, seed, offset, codes, scale, n, stream)):
+        return
     n = x.numel() if n is None else n
     _need(x, 4 * n, "x"); _need(codes, n * bits // 8, "codes"); _need(scale, 4 * _ng(n, group), "scale")
     _ck("sdp4_grad_quant_sr", lib().sdp4_grad_quant_sr(_ptr(x), n, bits, hadamard_block, group, seed, offset,
@@ -204,6 +262,9 @@ def sdp4_grad_quant_sr(x, bits, hadamard_block, group, seed, offset, codes, scal
 
 def sdp4_dequant_reduce_sr(codes, scales, n_chunk, bits_in, group, bits_out, seed, offset, out_codes, out_scales,
                            out_f32=None, stream=None):
+    if _fast is not None and _done("sdp4_dequant_reduce_sr", _fast.dequant_reduce_sr(
+            codes, scales, n_chunk, bits_in, group, bits_out, seed, offset, out_codes, out_scales, out_f32, stream)):
+        return
     P = len(codes)
     if len(scales) != P:
         raise ValueError("sdp4_dequant_reduce_sr: codes and scales differ in length")
