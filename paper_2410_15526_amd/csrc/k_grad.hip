@@ -22,25 +22,38 @@ template <int NB>
 struct GradQuant {
     static int run(const float *x, int64_t n, int bits, int gs, float cn, uint8_t *codes, float *scale, hipStream_t s)
     {
-        // (Times in us.)  4-bit codes: 16 elements per lane in 4-wave blocks, <= 6 per CU (32 per lane in 8-wave blocks <= 3:
-        // 2^20 / 2^23 / 2^25 / 2^27 elements 4.4 / 9.0 / 26.8 / 98.0, now 3.3 / 7.8 / 25.6 / 97.7).
-        if (bits == 4)
+        // Times in us, block 256 unless named.
+        if constexpr (NB <= 256) {
+            // 8 elements per lane: two stages fewer inside a lane are the DPP stages' gain, and 2 KiB read per
+            // wave streams best.  8-wave blocks <= 4 per CU, or below 2^25 elements (groups that fit a wave)
+            // 4-wave blocks <= 8, which spread a short launch better (8-bit, 2^21 / 2^23 / 2^24 / 2^25 / 2^27
+            // elements, 8-wave 3.9 / 8.9 / 15.4 / 27.6 / 105.2, 4-wave 3.55 / 8.35 / 14.8 / 27.9 / 105.7).  16
+            // per lane in 4-wave blocks, 8-bit <= 5 at 2^27 107.5; 4-bit <= 6 / 5 / 4 at 201326592 without a
+            // transform 146.6 / 142.9 / 139.8, now 139.1, and with block 128 146.0 / 144.3 / 147.0, now 141.9.
+            if (bits == 4)
+                return few<4>(x, n, gs, cn, codes, scale, s);
+            if constexpr (NB > 0)
+                return few<8>(x, n, gs, cn, codes, scale, s);
+            // 8-bit codes without a transform: 16 per lane, <= 4 per CU (2^27 elements <= 4 / 5 / 6 105.7 /
+            // 109.5 / 110.7, 8 per lane 106.2 and 3 to 5 % slower below 2^23).
+            return quantize<8, 16, 0, 4>(x, n, gs, cn, codes, scale, 4, s);
+        } else {
+            // Wider transforms cross rows of 16 lanes, less often the more elements a lane holds (8-bit, block
+            // 512 / 1024 at 2^27: 106.9 / 107.6 with 16 per lane, 107.6 / 112 with 8).
+            return bits == 4 ? quantize<4, 16, NB, 4>(x, n, gs, cn, codes, scale, 6, s)
+                             : quantize<8, 16, NB, 4>(x, n, gs, cn, codes, scale, 5, s);
+        }
+    }
+
+private:
+    template <int BITS>
+    static int few(const float *x, int64_t n, int gs, float cn, uint8_t *codes, float *scale, hipStream_t s)
+    {
+        if (n < (int64_t(1) << 25) && gs <= 9)
+            return quantize<BITS, 8, NB, 4>(x, n, gs, cn, codes, scale, 8, s);
+        if constexpr (BITS == 4 && NB == 256) // 4-bit codes, 2^27 / 2^29 elements: 98.3 / 390, with 8 per lane 99.3 / 396
             return quantize<4, 16, NB, 4>(x, n, gs, cn, codes, scale, 6, s);
-        // 8-bit codes without a transform: <= 4 per CU (<= 5 / 6: 2^27 elements 109.5 / 110.7, now 105.7).
-        if constexpr (NB == 0)
-            return quantize<8, 16, NB, 4>(x, n, gs, cn, codes, scale, 4, s);
-        // Transforms up to 256 points: 8 elements per lane, whose two stages fewer inside a lane are the DPP
-        // stages' gain; 8-wave blocks <= 4 per CU, or below 2^25 elements (groups that fit a wave) 4-wave
-        // blocks <= 8, which spread a short launch better (2^21 / 2^23 / 2^24 / 2^25 / 2^27 elements, block
-        // 256, 8-wave 3.9 / 8.9 / 15.4 / 27.6 / 105.2, 4-wave 3.55 / 8.35 / 14.8 / 27.9 / 105.7; 16 per lane
-        // in 4-wave blocks <= 5 at 2^27 107.5).
-        else if constexpr (NB <= 256)
-            return n < (int64_t(1) << 25) && gs <= 9 ? quantize<8, 8, NB, 4>(x, n, gs, cn, codes, scale, 8, s)
-                                                     : quantize<8, 8, NB, 8>(x, n, gs, cn, codes, scale, 4, s);
-        // Wider ones cross rows of 16 lanes, the fewer the more elements a lane holds (block 512 / 1024 at
-        // 2^27: 106.9 / 107.6 with 16 per lane, 107.6 / 112 with 8).
-        else
-            return quantize<8, 16, NB, 4>(x, n, gs, cn, codes, scale, 5, s);
+        return quantize<BITS, 8, NB, 8>(x, n, gs, cn, codes, scale, 4, s);
     }
 };
 

@@ -6,16 +6,14 @@ namespace sdp4 {
 
 namespace {
 
-// 16 elements per lane in blocks of 4 waves, <= 3 per CU (2^27 elements, <= 3 / 4 / 5 / 6 per CU:
-// bfloat16 weights 139.7 / 143 / 141.4 / 142.2 us, float32 179.6 / 182.4 / 184.2 / 186.0).
-template <bool WIDE>
+template <int WPB, bool WIDE>
 int qwd_encode(const float *w_new, const void *w_prev, bool bf16, bool sym, int64_t n, int gs, uint8_t *codes,
-               float *scale, float *minv, hipStream_t s)
+               float *scale, float *minv, int cap, hipStream_t s)
 {
-    constexpr int E = 16, WPB = 4;
+    constexpr int E = 16;
     auto k = bf16 ? (sym ? k_qwd_encode<true, true, E, WPB, WIDE> : k_qwd_encode<true, false, E, WPB, WIDE>)
                   : (sym ? k_qwd_encode<false, true, E, WPB, WIDE> : k_qwd_encode<false, false, E, WPB, WIDE>);
-    return launch_tiles<E, WPB>(k, n, 3, s, w_new, w_prev, n, gs, codes, scale, minv);
+    return launch_tiles<E, WPB>(k, n, cap, s, w_new, w_prev, n, gs, codes, scale, minv);
 }
 
 // 2-wave blocks, <= 8 per CU, 16 elements per lane for bfloat16 weights and 8 for float32: 2 KiB of weights
@@ -35,10 +33,16 @@ int qwd_decode(const uint8_t *codes, const float *scale, const float *minv, int6
 int launch_qwd_encode(const float *w_new, const void *w_prev, bool bf16, bool sym, int64_t n, int group,
                       uint8_t *codes, float *scale, float *minv, hipStream_t s)
 {
+    // 16 elements per lane, 12 waves per CU: 4-wave blocks <= 3 (2^27 elements, <= 3 / 4 / 5 / 6 per CU: bfloat16
+    // weights 139.7 / 143 / 141.4 / 142.2 us, float32 179.6 / 182.4 / 184.2 / 186.0), or, for large launches with
+    // bfloat16 weights, 2-wave blocks <= 6 (2^30 elements 1114 against 1145, 201M 208.7 against 210.1; 50M 53.2
+    // against 53.0; float32 weights at 2^30 1465 against 1450).
     const int gs = log2_of(group);
     if (group > kWave * 16) // beyond a wave tile
-        return qwd_encode<true>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, s);
-    return qwd_encode<false>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, s);
+        return qwd_encode<4, true>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, 3, s);
+    if (bf16 && n >= (int64_t(1) << 27))
+        return qwd_encode<2, false>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, 6, s);
+    return qwd_encode<4, false>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, 3, s);
 }
 
 int launch_qwd_decode(const uint8_t *codes, const float *scale, const float *minv, int64_t n,

@@ -672,7 +672,10 @@ int requant_groups(const PeerTable &peers, int P, int64_t n, int gs, int cap, ui
 // 8-wave blocks.  (us, 8 to 4 bits, 2^29 input elements, 4-wave <= 4 / 5 / 8
 // and 8-wave <= 3 per CU: P = 1 - / 186 / 157 / 162, P = 2 124 / - / 107 / 117,
 // P = 3 112 / 103 / 105 / 99, P = 4 102 / 103 / 101 / 105, P = 8 93.1 / 94.4 /
-// 94.7 / 94; 2^22 with P = 8 3.1 in 4-wave blocks, 3.8 in 8-wave ones.)
+// 94.7 / 94; 2^22 with P = 8 3.1 in 4-wave blocks, 3.8 in 8-wave ones.)  8
+// peers with chunks of 2^26 elements and more take 8-wave blocks <= 2 (chunks
+// of 105M / 203M: 140.4 / 277.5 against 146.9 / 285.6 in 4-wave ones; of 25M
+// 37.2 against 36.8).
 // 4-bit messages: 4-wave blocks, 32 elements per lane (a 16-byte chunk per
 // peer) <= 6 per CU for the large launches of up to 7 peers, else 16 per lane
 // <= 8 (2^29 input elements, P = 4 56.3 against 59.7 with 16 per lane; P = 8
@@ -688,9 +691,9 @@ int requant_any(const PeerTable &peers, int P, int64_t n, int gs, uint8_t *out_c
         return requant_groups<4, BITS_OUT, 16, 4, SR>(peers, P, n, gs, 8, out_codes, out_scales, out_f32, s, seed,
                                                       offset);
     } else {
-        if (P & (P - 1))
-            return requant_groups<8, BITS_OUT, 16, 8, SR>(peers, P, n, gs, 3, out_codes, out_scales, out_f32, s, seed,
-                                                          offset);
+        if (P & (P - 1) || (P == 8 && n >= (int64_t(1) << 26)))
+            return requant_groups<8, BITS_OUT, 16, 8, SR>(peers, P, n, gs, P == 8 ? 2 : 3, out_codes, out_scales,
+                                                          out_f32, s, seed, offset);
         return requant_groups<8, BITS_OUT, 16, 4, SR>(peers, P, n, gs, P >= 4 ? 4 : 8, out_codes, out_scales, out_f32,
                                                       s, seed, offset);
     }

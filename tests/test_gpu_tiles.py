@@ -176,3 +176,48 @@ def test_stochastic_rounding_of_group_extremes(bits):
         want = oracle.grad_quant_sr(x, bits, 0, group, seed, 0)
         assert np.array_equal(host(codes), np.ascontiguousarray(want[0]).view(np.uint8))
         assert np.array_equal(host(scale), want[1])
+
+
+@pytest.mark.parametrize("bits,block", [(8, 256), (4, 0), (4, 128), (4, 256)])
+@pytest.mark.parametrize("extra", [-512, 512])
+def test_grad_quant_around_its_block_shape_switch(bits, block, extra):
+    n, group = (1 << 25) + extra, 512
+    say(f"grad_quant bits={bits} block={block} n={n}")
+    x = np.random.default_rng(bits).standard_normal(n, dtype=np.float32)
+    codes, scale = empty(n * bits // 8, "u8"), empty(n // group, "f32")
+    sdp4.sdp4_grad_quant(dev(x), bits, block, group, codes, scale)
+    sync()
+    want = oracle.grad_quant(x, bits, block, group)
+    assert np.array_equal(host(codes), np.ascontiguousarray(want[0]).view(np.uint8))
+    assert np.array_equal(host(scale), want[1])
+
+
+@pytest.mark.parametrize("group,extra", [(128, 0), (1024, 1024), (2048, 0)])
+def test_bf16_encode_at_its_block_shape_switch(group, extra):
+    n = (1 << 27) + extra
+    say(f"encode bf16 n={n} group={group}")
+    new, prev = _weights(1 << 20, True, group)
+    reps = n // (1 << 20) + 1
+    new_d, prev_d = dev(new).repeat(reps)[:n].clone(), dev(prev).repeat(reps)[:n].clone()
+    codes, scale, minv = empty(n // 2, "u8"), empty(n // group, "f32"), empty(n // group, "f32")
+    sdp4.sdp4_qwd_encode(new_d, prev_d, group, codes, scale, minv)
+    want = [dev(a) for a in oracle.qwd_encode(new, prev, group)[:3]]
+    t = torch()
+    for got, w in zip((codes, scale, minv), want):
+        assert t.equal(got, w.repeat(reps)[:got.numel()])
+
+
+def test_requant_of_8_peers_at_its_block_shape_switch():
+    """Chunks of 2^26 elements and one group more; the peers share one message."""
+    group, n = 4096, (1 << 26) + 4096
+    say(f"requant P=8 n={n}")
+    (c, s), = _messages(1, 1 << 20, 8, group, 9)
+    reps = n // (1 << 20) + 1
+    cd, sd = dev(c).repeat(reps)[:n].clone(), dev(s).repeat(reps)[:n // group].clone()
+    want = oracle.dequant_reduce([c] * 8, [s] * 8, 1 << 20, 8, group, 4)
+    wc, ws = dev(np.ascontiguousarray(want["codes"]).view(np.uint8)), dev(want["scales"])
+    t = torch()
+    for m in (n - 4096, n):
+        oc, osc = empty(m // 2, "u8"), empty(m // group, "f32")
+        sdp4.sdp4_dequant_reduce([cd] * 8, [sd] * 8, m, 8, group, 4, out_codes=oc, out_scales=osc)
+        assert t.equal(oc, wc.repeat(reps)[:m // 2]) and t.equal(osc, ws.repeat(reps)[:m // group])
