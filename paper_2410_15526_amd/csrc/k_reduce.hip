@@ -136,10 +136,10 @@ int launch_dequant_reduce(const PeerTable &peers, int P, int64_t n, int bits_in,
                    : launch_dequant_reduce_f32_in4(peers, P, n, group, nblk, cn, out_scale, out_f32, s);
     const int gs = log2_of(group);
     if (bits_in == 8)
-        return bits_out == 4 ? requant_any<8, 4, false>(peers, P, n, gs, out_codes, out_scales, out_f32, s, 0, 0)
-                             : requant_any<8, 8, false>(peers, P, n, gs, out_codes, out_scales, out_f32, s, 0, 0);
-    return bits_out == 4 ? requant_any<4, 4, false>(peers, P, n, gs, out_codes, out_scales, out_f32, s, 0, 0)
-                         : requant_any<4, 8, false>(peers, P, n, gs, out_codes, out_scales, out_f32, s, 0, 0);
+        return bits_out == 4 ? requant_for<8, 4, false>(peers, P, n, gs, out_codes, out_scales, out_f32, s, 0, 0)
+                             : requant_for<8, 8, false>(peers, P, n, gs, out_codes, out_scales, out_f32, s, 0, 0);
+    return bits_out == 4 ? requant_for<4, 4, false>(peers, P, n, gs, out_codes, out_scales, out_f32, s, 0, 0)
+                         : requant_for<4, 8, false>(peers, P, n, gs, out_codes, out_scales, out_f32, s, 0, 0);
 }
 
 // Blocks of a kernel that loops with the stride of a one-dimensional grid.

@@ -47,11 +47,11 @@ int launch_dequant_reduce_sr(const PeerTable &peers, int P, int64_t n, int bits_
     const int gs = log2_of(group);
     if (bits_in == 8)
         return bits_out == 4
-                   ? requant_any<8, 4, true>(peers, P, n, gs, out_codes, out_scales, out_f32, s, seed, offset)
-                   : requant_any<8, 8, true>(peers, P, n, gs, out_codes, out_scales, out_f32, s, seed, offset);
+                   ? requant_for<8, 4, true>(peers, P, n, gs, out_codes, out_scales, out_f32, s, seed, offset)
+                   : requant_for<8, 8, true>(peers, P, n, gs, out_codes, out_scales, out_f32, s, seed, offset);
     return bits_out == 4
-               ? requant_any<4, 4, true>(peers, P, n, gs, out_codes, out_scales, out_f32, s, seed, offset)
-               : requant_any<4, 8, true>(peers, P, n, gs, out_codes, out_scales, out_f32, s, seed, offset);
+               ? requant_for<4, 4, true>(peers, P, n, gs, out_codes, out_scales, out_f32, s, seed, offset)
+               : requant_for<4, 8, true>(peers, P, n, gs, out_codes, out_scales, out_f32, s, seed, offset);
 }
 
 } // namespace sdp4

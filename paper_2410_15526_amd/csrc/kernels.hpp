@@ -625,107 +625,163 @@ int launch_tiles(void (*kernel)(Params...), int64_t n, int cap, hipStream_t s, A
     return launch<WPB>(kernel, (n + BT - 1) / BT, cap, s, args...);
 }
 
-// Re-quantizing dequantize-reduce.  The peer counts of power-of-two nodes have
-// instantiations of their own, without tests of P between the loads (2^27
-// input elements, against the guarded form on the same box: 4 to 4 bits
-// 18.6 -> 17.5 us with 4 peers and 18.0 -> 16.0 with 16, 8 to 4 bits of small
-// chunks 3.6 -> 3.2); the float32 copy of the sums, and other counts, take
-// the guarded one of up to 4, 8 or 16 peers.
+// A set of peer counts: bit p for p peers.
+constexpr uint32_t peer_range(int lo, int hi) { return (2u << hi) - (1u << lo); }
+constexpr uint32_t kAllPeers = peer_range(1, 16);
+
+// Calls `go` with the kernel for P peers, a count of the set PEERS: K<PMAX,
+// EXACT>::get() is one with PMAX peers (EXACT) or with up to PMAX.  1 to 8 and
+// 16 peers have instantiations of their own, without tests of P between the
+// loads (2^27 input elements, against the guarded form on the same box: 4 to 4
+// bits 18.6 -> 17.5 us with 4 peers and 18.0 -> 16.0 with 16, 8 to 4 bits of
+// small chunks 3.6 -> 3.2); other counts, and with GUARDED whatever `guarded`
+// asks for, take the guarded one.
+template <template <int, bool> class K, uint32_t PEERS, bool GUARDED, class Go>
+int with_peers(int P, bool guarded, Go go)
+{
+    const auto exact = [&](auto count, int &rc) {
+        constexpr int N = decltype(count)::value;
+        if constexpr (PEERS >> N & 1) {
+            if (P == N && !guarded) {
+                rc = go(K<N, true>::get());
+                return true;
+            }
+        }
+        return false;
+    };
+    int rc = 0;
+    if (exact(std::integral_constant<int, 1>{}, rc) || exact(std::integral_constant<int, 2>{}, rc) ||
+        exact(std::integral_constant<int, 3>{}, rc) || exact(std::integral_constant<int, 4>{}, rc) ||
+        exact(std::integral_constant<int, 5>{}, rc) || exact(std::integral_constant<int, 6>{}, rc) ||
+        exact(std::integral_constant<int, 7>{}, rc) || exact(std::integral_constant<int, 8>{}, rc) ||
+        exact(std::integral_constant<int, 16>{}, rc))
+        return rc;
+    if constexpr (GUARDED && (PEERS & peer_range(1, 4))) {
+        if (P <= 4)
+            return go(K<4, false>::get());
+    }
+    if constexpr (GUARDED && (PEERS & peer_range(5, 8))) {
+        if (P <= 8)
+            return go(K<8, false>::get());
+    }
+    if constexpr (PEERS & (GUARDED ? peer_range(9, 16) : peer_range(9, 15)))
+        return go(K<16, false>::get());
+    return 1; // not reached: P is in PEERS
+}
+
+// Re-quantizing dequantize-reduce of PEERS peers, in blocks of WPB waves, <= cap
+// per CU; groups beyond a wave tile are shared by the waves of a block.
+// The optional float32 copy of the sums is the guarded kernels'.
 template <int BITS_IN, int BITS_OUT, int E, int WPB, bool SR, bool WIDE>
+struct Requant {
+    template <int PMAX, bool EXACT>
+    struct Kernel {
+        static auto get() { return k_requant<BITS_IN, BITS_OUT, E, PMAX, EXACT, WPB, SR, WIDE>; }
+    };
+};
+
+template <int BITS_IN, int BITS_OUT, int E, int WPB, bool SR, uint32_t PEERS>
 int requant(const PeerTable &peers, int P, int64_t n, int gs, int cap, uint8_t *out_codes, float *out_scales,
             float *out_f32, hipStream_t s, uint64_t seed, uint64_t offset)
 {
     const auto go = [&](auto kernel) {
         return launch_tiles<E, WPB>(kernel, n, cap, s, peers, P, n, gs, out_codes, out_scales, out_f32, seed, offset);
     };
-    if (!out_f32) {
-        switch (P) {
-        case 2: return go(k_requant<BITS_IN, BITS_OUT, E, 2, true, WPB, SR, WIDE>);
-        case 3: return go(k_requant<BITS_IN, BITS_OUT, E, 3, true, WPB, SR, WIDE>);
-        case 4: return go(k_requant<BITS_IN, BITS_OUT, E, 4, true, WPB, SR, WIDE>);
-        case 8: return go(k_requant<BITS_IN, BITS_OUT, E, 8, true, WPB, SR, WIDE>);
-        case 16: return go(k_requant<BITS_IN, BITS_OUT, E, 16, true, WPB, SR, WIDE>);
-        default: break;
-        }
-    }
-    return P <= 4   ? go(k_requant<BITS_IN, BITS_OUT, E, 4, false, WPB, SR, WIDE>)
-           : P <= 8 ? go(k_requant<BITS_IN, BITS_OUT, E, 8, false, WPB, SR, WIDE>)
-                    : go(k_requant<BITS_IN, BITS_OUT, E, 16, false, WPB, SR, WIDE>);
-}
-
-// Groups beyond a wave tile are shared by the waves of a block.
-template <int BITS_IN, int BITS_OUT, int E, int WPB, bool SR>
-int requant_groups(const PeerTable &peers, int P, int64_t n, int gs, int cap, uint8_t *out_codes, float *out_scales,
-                   float *out_f32, hipStream_t s, uint64_t seed, uint64_t offset)
-{
     if ((1 << gs) > kWave * E)
-        return requant<BITS_IN, BITS_OUT, E, WPB, SR, true>(peers, P, n, gs, cap, out_codes, out_scales, out_f32, s,
-                                                            seed, offset);
-    return requant<BITS_IN, BITS_OUT, E, WPB, SR, false>(peers, P, n, gs, cap, out_codes, out_scales, out_f32, s, seed,
-                                                         offset);
+        return with_peers<Requant<BITS_IN, BITS_OUT, E, WPB, SR, true>::template Kernel, PEERS, true>(P, out_f32, go);
+    return with_peers<Requant<BITS_IN, BITS_OUT, E, WPB, SR, false>::template Kernel, PEERS, true>(P, out_f32, go);
 }
 
-// 8-bit messages: 16 elements per lane, one 16-byte chunk per peer.  A wave
-// keeps P KiB in flight: power-of-two counts from 4 on take 4-wave blocks
-// <= 4 per CU, 1 and 2 peers <= 8; other counts, whose chunks lie at strides
-// that spread over the memory channels, run best with 24 waves per CU, in
-// 8-wave blocks.  (us, 8 to 4 bits, 2^29 input elements, 4-wave <= 4 / 5 / 8
-// and 8-wave <= 3 per CU: P = 1 - / 186 / 157 / 162, P = 2 124 / - / 107 / 117,
-// P = 3 112 / 103 / 105 / 99, P = 4 102 / 103 / 101 / 105, P = 8 93.1 / 94.4 /
-// 94.7 / 94; 2^22 with P = 8 3.1 in 4-wave blocks, 3.8 in 8-wave ones.)  8
-// peers with chunks of 2^26 elements and more take 8-wave blocks <= 2 (chunks
-// of 105M / 203M: 140.4 / 277.5 against 146.9 / 285.6 in 4-wave ones; of 25M
-// 37.2 against 36.8).
+// 8-bit messages: 16 elements per lane, one 16-byte chunk per peer; a wave
+// keeps P KiB in flight.  1 and 2 peers: 4-wave blocks, <= 8 per CU.  16 peers,
+// and short launches of 4 and 8: 4-wave blocks <= 4, which spread better.
+// Others: 8-wave blocks <= 3, or <= 2 for 8 peers with chunks of 2^26 elements
+// and more; they suffer less where the chunks of the peers lie a large power
+// of two apart (as those of power-of-two widths do) and their rows meet in
+// the same memory banks.  us, 8 to 4 bits, 4-wave <= 4 (<= 8 up to 3 peers)
+// against 8-wave <= 3:
+//   P = 8, chunks of 2^24 29.2 / 26.7, 2^24 + 12288 25.0 / 25.1, 5 * 2^22
+//     33.7 / 32.2, 26214400 37.4 / 37.9, 2^19 3.1 / 3.8; 105M and 203M 146.9 /
+//     285.6, 8-wave <= 2 140.4 / 277.5
+//   P = 4, 2^25 28.4 / 27.1, 2^25 + 12288 26.1 / 26.0; 2^27 101.6 / 103 or more
+//   P = 3, 60M 105 / 99;  P = 2, 134M 107 / 117;  P = 16, 2^23 28.3 / 29.0,
+//     2^23 + 6144 25.0 / 26.4
 // 4-bit messages: 4-wave blocks, 32 elements per lane (a 16-byte chunk per
 // peer) <= 6 per CU for the large launches of up to 7 peers, else 16 per lane
-// <= 8 (2^29 input elements, P = 4 56.3 against 59.7 with 16 per lane; P = 8
-// 53.8 with 32, 53.3 with 16, and at 2^22 4.9 and 4.5).
+// <= 8, or, from 8 peers and 2^22 elements on, in 8-wave blocks <= 4 (2^29 input
+// elements, P = 4 56.3 against 59.7 with 16 per lane; P = 8, chunks of 2^24 /
+// 2^24 + 12288 / 50.8M 4-wave 17.8 / 15.0 / 43.7, 8-wave 15.6 / 15.7 / 40.4).
+template <int E_, int WPB_, uint32_t PEERS_>
+struct Shape { // elements per lane, waves per block, peer counts that take it
+    static constexpr int E = E_, WPB = WPB_;
+    static constexpr uint32_t PEERS = PEERS_;
+};
+
 template <int BITS_IN, int BITS_OUT, bool SR>
-int requant_any(const PeerTable &peers, int P, int64_t n, int gs, uint8_t *out_codes, float *out_scales, float *out_f32,
+int requant_for(const PeerTable &peers, int P, int64_t n, int gs, uint8_t *out_codes, float *out_scales, float *out_f32,
                 hipStream_t s, uint64_t seed, uint64_t offset)
 {
+    const auto go = [&](auto shape, int cap) {
+        using S = decltype(shape);
+        return requant<BITS_IN, BITS_OUT, S::E, S::WPB, SR, S::PEERS>(peers, P, n, gs, cap, out_codes, out_scales, out_f32,
+                                                                    s, seed, offset);
+    };
     if constexpr (BITS_IN == 4) {
-        if (P < 8 && n >= (int64_t(1) << 22))
-            return requant_groups<4, BITS_OUT, 32, 4, SR>(peers, P, n, gs, 6, out_codes, out_scales, out_f32, s, seed,
-                                                          offset);
-        return requant_groups<4, BITS_OUT, 16, 4, SR>(peers, P, n, gs, 8, out_codes, out_scales, out_f32, s, seed,
-                                                      offset);
+        if (n < (int64_t(1) << 22))
+            return go(Shape<16, 4, kAllPeers>{}, 8);
+        return P < 8 ? go(Shape<32, 4, peer_range(1, 7)>{}, 6) : go(Shape<16, 8, peer_range(8, 16)>{}, 4);
     } else {
-        if (P & (P - 1) || (P == 8 && n >= (int64_t(1) << 26)))
-            return requant_groups<8, BITS_OUT, 16, 8, SR>(peers, P, n, gs, P == 8 ? 2 : 3, out_codes, out_scales,
-                                                          out_f32, s, seed, offset);
-        return requant_groups<8, BITS_OUT, 16, 4, SR>(peers, P, n, gs, P >= 4 ? 4 : 8, out_codes, out_scales, out_f32,
-                                                      s, seed, offset);
+        const bool large = n >= (int64_t(1) << 26), small = n < (int64_t(1) << 23);
+        if (P & (P - 1) || (P == 8 && !small) || (P == 4 && !small && !large))
+            return go(Shape<16, 8, peer_range(3, 15)>{}, P == 8 && large ? 2 : 3);
+        return go(Shape<16, 4, (1u << 1 | 1u << 2 | 1u << 4 | 1u << 8 | 1u << 16)>{}, P >= 4 ? 4 : 8);
     }
 }
 
-// Dequantize-reduce to float32: 16 elements per lane in blocks of 4 waves
-// (4 KiB written per wave).  us, 2^29 input elements: 4-bit messages with
-// P = 4, <= 4 / 5 / 6 / 8 per CU 124 / 126 / 126 / 128, P = 2 216 / 208 / 212 /
-// 242, with 32 elements per lane P = 4 133, P = 16 71 against 67 (and 2^18,
-// P = 16, 4.9 against 3.6); 8-bit ones with P = 2 <= 4 / 5 / 6 / 8 243 / 247 /
-// 261 / 281, P = 1 2 to 5 % faster at <= 5.
+template <int BITS_IN, int NB, int E, int WPB>
+struct ReduceToF32 {
+    template <int PMAX, bool EXACT>
+    struct Kernel {
+        static auto get() { return k_reduce_to_f32<BITS_IN, E, NB, PMAX, EXACT, WPB>; }
+    };
+};
+
+// Dequantize-reduce to float32: 16 elements per lane (4 KiB written per wave).
+// 8-bit messages in 4-wave blocks, <= 5 per CU for one peer, <= 4 for more (us,
+// 2^29 input elements, <= 4 / 5 / 6 / 8 per CU: P = 2 243 / 247 / 261 / 281; P = 1
+// 2 to 5 % faster at 5).  4-bit messages: from 8 peers on 8-wave blocks <= 3 for
+// all but short launches (P = 8, chunks of 2^24 / 50.8M 24.9 / 67.7, 4-wave <= 4
+// 26.9 / 71.4; P = 16, 2^23 20.2 and 24.3); fewer peers in 4-wave blocks, <= 4
+// from 4 peers on, <= 5 below (2^29 input elements, P = 2 <= 4 / 5 / 6 / 8 216 /
+// 208 / 212 / 242), but 4 peers with chunks of 2^24 and more in 2-wave blocks <= 8
+// (50.8M 50.4, 4-wave <= 4 52.0).  32 elements per lane, 8 KiB written per wave,
+// are slower in general (P = 4, 2^29 133, with 16 124; 2^21 4.5 and 4.1) and
+// faster for 3 and 4 peers while the result is of the order of the last-level
+// caches (28 to 48 MB: P = 4, 7340032 / 2^23 / 9437184 7.8 / 8.9 / 10.8, with 16
+// per lane 9.5 / 11.3 / 12.4; 6291456 and 12582912 the same either way), and
+// for 5 to 7 peers from there on (P = 5, 2^23 10.9, with 16 12.2).
 template <int BITS_IN, int NB>
 int reduce_to_f32(const PeerTable &peers, int P, int64_t n, int gs, float cn, float out_scale, float *out_f32,
-                  hipStream_t s)
+                      hipStream_t s)
 {
-    constexpr int E = 16, WPB = 4;
-    const int cap = BITS_IN == 4 ? (P >= 4 ? 4 : 5) : (P >= 2 ? 4 : 5);
-    const auto go = [&](auto kernel) {
-        return launch_tiles<E, WPB>(kernel, n, cap, s, peers, P, n, gs, cn, out_scale, out_f32);
+    const auto go = [&](auto shape, int cap) {
+        using S = decltype(shape);
+        return with_peers<ReduceToF32<BITS_IN, NB, S::E, S::WPB>::template Kernel, S::PEERS, false>(
+            P, false, [&](auto kernel) {
+                return launch_tiles<S::E, S::WPB>(kernel, n, cap, s, peers, P, n, gs, cn, out_scale, out_f32);
+            });
     };
-    switch (P) {
-    case 1: return go(k_reduce_to_f32<BITS_IN, E, NB, 1, true, WPB>);
-    case 2: return go(k_reduce_to_f32<BITS_IN, E, NB, 2, true, WPB>);
-    case 3: return go(k_reduce_to_f32<BITS_IN, E, NB, 3, true, WPB>);
-    case 4: return go(k_reduce_to_f32<BITS_IN, E, NB, 4, true, WPB>);
-    case 8: return go(k_reduce_to_f32<BITS_IN, E, NB, 8, true, WPB>);
-    case 16: return go(k_reduce_to_f32<BITS_IN, E, NB, 16, true, WPB>);
-    default: break;
+    if constexpr (BITS_IN == 4) {
+        if (P >= 8 && n >= (int64_t(1) << 21))
+            return go(Shape<16, 8, peer_range(8, 16)>{}, 3);
+        if (P >= 3 && P < 8 && n >= (int64_t(7) << 20) && (P > 4 || n < (int64_t(12) << 20)))
+            return go(Shape<32, 4, peer_range(3, 7)>{}, 4);
+        if (P == 4 && n >= (int64_t(1) << 24))
+            return go(Shape<16, 2, 1u << 4>{}, 8);
+        return go(Shape<16, 4, kAllPeers>{}, P >= 4 ? 4 : 5);
+    } else {
+        return go(Shape<16, 4, kAllPeers>{}, P >= 2 ? 4 : 5);
     }
-    return P <= 4   ? go(k_reduce_to_f32<BITS_IN, E, NB, 4, false, WPB>)
-           : P <= 8 ? go(k_reduce_to_f32<BITS_IN, E, NB, 8, false, WPB>)
-                    : go(k_reduce_to_f32<BITS_IN, E, NB, 16, false, WPB>);
 }
 
 } // namespace sdp4

@@ -221,3 +221,36 @@ def test_requant_of_8_peers_at_its_block_shape_switch():
         oc, osc = empty(m // 2, "u8"), empty(m // group, "f32")
         sdp4.sdp4_dequant_reduce([cd] * 8, [sd] * 8, m, 8, group, 4, out_codes=oc, out_scales=osc)
         assert t.equal(oc, wc.repeat(reps)[:m // 2]) and t.equal(osc, ws.repeat(reps)[:m // group])
+
+
+# Chunk sizes on either side of every switch of the float32 reduction of 4-bit messages: 2^21 elements for
+# 8 and more peers, 7 and 12 times 2^20 for 3 to 7, 2^24 for 4.
+@pytest.mark.parametrize("P,n", [(16, (1 << 21) - 256), (9, 1 << 21), (3, (7 << 20) - 256), (3, 7 << 20), (4, 12 << 20),
+                                 (5, (7 << 20) + 256), (4, (1 << 24) - 256), (4, (1 << 24) + 256), (2, 7 << 20)])
+@pytest.mark.parametrize("group,block", [(128, 256), (32, 0)])
+def test_4_bit_reduction_to_f32_around_its_shape_switches(P, n, group, block):
+    say(f"reduce f32 P={P} n={n} group={group} block={block}")
+    msgs = _messages(1, 1 << 20, 4, group, P + n)
+    c = [np.resize(np.roll(msgs[0][0], 16 * group * p), n // 2) for p in range(P)]
+    s = [np.resize(np.roll(msgs[0][1], p), n // group) for p in range(P)]
+    out = empty(n, "f32")
+    sdp4.sdp4_dequant_reduce([dev(x) for x in c], [dev(x) for x in s], n, 4, group, 0, block, 0.25, out_f32=out)
+    sync()
+    ref = oracle.dequant_reduce(c, s, n, 4, group, 0, block, 0.25)
+    check_f32(host(out), ref["f32"])
+
+
+@pytest.mark.parametrize("P,n", [(4, 1 << 23), (8, (1 << 23) - 4096), (8, 1 << 23), (5, 3 << 12), (16, 1 << 22)])
+@pytest.mark.parametrize("bits_in", [4, 8])
+def test_requant_around_its_block_shape_switches(P, n, bits_in):
+    group = 4096
+    say(f"requant P={P} n={n} bits={bits_in}")
+    msgs = _messages(1, min(n, 1 << 20), bits_in, group, P)
+    c = [np.resize(np.roll(msgs[0][0], 16 * p), n * bits_in // 8) for p in range(P)]
+    s = [np.resize(np.roll(msgs[0][1], p), n // group) for p in range(P)]
+    oc, osc = empty(n // 2, "u8"), empty(n // group, "f32")
+    sdp4.sdp4_dequant_reduce([dev(x) for x in c], [dev(x) for x in s], n, bits_in, group, 4, out_codes=oc, out_scales=osc)
+    sync()
+    ref = oracle.dequant_reduce(c, s, n, bits_in, group, 4)
+    assert np.array_equal(host(oc), np.ascontiguousarray(ref["codes"]).view(np.uint8))
+    assert np.array_equal(host(osc), ref["scales"])
