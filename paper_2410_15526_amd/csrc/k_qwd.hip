@@ -38,8 +38,12 @@ int launch_qwd_encode(const float *w_new, const void *w_prev, bool bf16, bool sy
     // bfloat16 weights, 2-wave blocks <= 6 (2^30 elements 1114 against 1145, 201M 208.7 against 210.1; 50M 53.2
     // against 53.0; float32 weights at 2^30 1465 against 1450).
     const int gs = log2_of(group);
-    if (group > kWave * 16) // beyond a wave tile
-        return qwd_encode<4, true>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, 3, s);
+    if (group > kWave * 16) { // beyond a wave tile; bfloat16 weights <= 4 (groups of 4096 at 1.6e9 1641, <= 3 1664),
+        // or large launches whose groups two waves hold as below (2048 at 1.6e9 1699, 4-wave <= 4 1709, <= 3 1718)
+        if (bf16 && group == 2048 && n >= (int64_t(1) << 28))
+            return qwd_encode<2, true>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, 6, s);
+        return qwd_encode<4, true>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, bf16 ? 4 : 3, s);
+    }
     if (bf16 && n >= (int64_t(1) << 27))
         return qwd_encode<2, false>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, 6, s);
     return qwd_encode<4, false>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, 3, s);

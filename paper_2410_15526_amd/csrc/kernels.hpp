@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kWave * WPB) void k_qwd_encode(
     uint8_t *__restrict__ codes, float *__restrict__ scale, float *__restrict__ minv)
 {
     using Pl = Place<E, WPB>;
-    static_assert(!WIDE || Pl::BT >= 4096, "a group within one block");
+    static_assert(!WIDE || Pl::BT >= 2048, "a group (2 waves: of at most 2048 elements) within one block");
     constexpr int R = E / 4;
     constexpr int RP = BF16 ? E / 8 : E / 4;
     __shared__ u32x4 lds_all[WPB][kWave * R];

@@ -192,9 +192,9 @@ def test_grad_quant_around_its_block_shape_switch(bits, block, extra):
     assert np.array_equal(host(scale), want[1])
 
 
-@pytest.mark.parametrize("group,extra", [(128, 0), (1024, 1024), (2048, 0)])
-def test_bf16_encode_at_its_block_shape_switch(group, extra):
-    n = (1 << 27) + extra
+@pytest.mark.parametrize("group,n", [(128, 1 << 27), (1024, (1 << 27) + 1024), (2048, (1 << 28) - 2048),
+                                     (2048, (1 << 28) + 2048)])
+def test_bf16_encode_at_its_block_shape_switches(group, n):
     say(f"encode bf16 n={n} group={group}")
     new, prev = _weights(1 << 20, True, group)
     reps = n // (1 << 20) + 1
