@@ -588,6 +588,14 @@ __global__ __launch_bounds__(kWave * WPB) void k_hadamard(const float *x, float 
         fwht_lane<E, NB>(v, cn);
         f32_to_chunks<E>(v, c);
         store_chunks<WHOLE>(y + at.base, at.wave, at.lane, valid / 4, lds, c, at.lane);
+        if constexpr (NB == 2 && !WHOLE) { // 16-byte chunks leave the last pair of n = 4k + 2 elements
+            if (valid % 4 != 0 && at.lane == 0) {
+                const int64_t i = at.base + at.wave * Pl::W + valid - 2;
+                const float a = x[i], b = x[i + 1];
+                y[i] = (a + b) * cn;
+                y[i + 1] = (a - b) * cn;
+            }
+        }
     });
 }
 

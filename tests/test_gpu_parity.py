@@ -403,6 +403,21 @@ def test_hadamard(block):
     check_f32(host(xd), want, "in place")
 
 
+@pytest.mark.parametrize("n", [2, 6, 1022, 1026, 4094, 4096 + 2, 3 * 4096 + 2050])
+def test_hadamard_of_pairs_that_end_inside_a_16_byte_chunk(n):
+    """Block 2 admits any even n: the last pair, in every wave's place, is transformed too."""
+    say(f"hadamard block=2 n={n}")
+    x = grad_input(n, seed=n)
+    pad = np.float32([7.0, -7.0])                      # what lies behind the array stays as it is
+    xd, y = dev(np.concatenate([x, pad])), dev(np.concatenate([np.zeros(n, np.float32), pad]))
+    sdp4.sdp4_hadamard(xd, y, 2, n=n)
+    sdp4.sdp4_hadamard(xd, xd, 2, n=n)                 # in place
+    sync()
+    want = np.concatenate([oracle.hadamard(x, 2), pad])
+    check_f32(host(y), want)
+    check_f32(host(xd), want, "in place")
+
+
 @pytest.mark.parametrize("P", [1, 2, 5, 16])
 @pytest.mark.parametrize("n", [4096, 4099, 1 << 20])
 def test_reduce_f32_and_copy(P, n):
