@@ -2,8 +2,9 @@
 
 Usable as ``python -m paper_2410_15526_amd.build``.  Each source compiles
 to an object under ``_build/`` (in parallel), then one shared library is
-linked next to this file, and with it ``_binding.so``, the Python binding's
-argument marshalling (a CPython extension on torch's headers).
+linked next to this file.  Where a ROCm build of torch is installed, so is
+``_binding.so``, the Python binding's argument marshalling (a CPython
+extension on torch's headers); the library itself needs only hipcc.
 """
 from __future__ import annotations
 
@@ -49,11 +50,17 @@ def _compile(src: str, bdir: str, defines) -> str:
     return obj
 
 
-def build_binding(out: str = BINDING) -> str:
-    """Compile ``_binding.so`` with g++ (host code only)."""
+def build_binding(out: str = BINDING) -> str | None:
+    """Compile ``_binding.so`` with g++ (host code only); None, with nothing
+    built, where there is no torch for it or torch is not a ROCm build."""
     import sysconfig
 
-    import torch
+    try:
+        import torch
+    except ImportError:
+        return None
+    if torch.version.hip is None:
+        return None
     troot = os.path.dirname(torch.__file__)
     tmp = out + f".tmp{os.getpid()}"
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
@@ -77,16 +84,16 @@ def build(verbose: bool = False, defines=(), out: str | None = None, build_dir: 
     lib = out or LIB
     os.makedirs(bdir, exist_ok=True)
     with cf.ThreadPoolExecutor(len(SOURCES) + 1) as ex:
-        binding = ex.submit(build_binding) if out is None else None
+        binding = ex.submit(build_binding, BINDING) if out is None else None
         objs = list(ex.map(lambda s: _compile(s, bdir, defines), SOURCES))
-        if binding is not None:
-            binding.result()
     tmp = lib + f".tmp{os.getpid()}"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, lib)
+    if binding is not None and binding.result() is None and verbose:
+        print("no ROCm build of torch: _binding.so is left out")
     if verbose:
         print(f"built {lib}")
     return lib
