@@ -64,7 +64,8 @@ def build_binding(out: str = BINDING) -> str | None:
     troot = os.path.dirname(torch.__file__)
     tmp = out + f".tmp{os.getpid()}"
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__=1",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INCLUDE,
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DSDP4_TORCH_VERSION="{torch.__version__}"', "-I", INCLUDE,
            "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(troot, "include"),
            "-isystem", os.path.join(troot, "include", "torch", "csrc", "api", "include"),
            "-isystem", os.path.join(os.path.dirname(os.path.dirname(hipcc())), "include"),

@@ -411,4 +411,10 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, method
 
 } // namespace
 
-PyMODINIT_FUNC PyInit__binding() { return PyModule_Create(&module_def); }
+PyMODINIT_FUNC PyInit__binding()
+{
+    PyObject *m = PyModule_Create(&module_def);
+    if (m && PyModule_AddStringConstant(m, "torch_version", SDP4_TORCH_VERSION) < 0)
+        Py_CLEAR(m);
+    return m;
+}

@@ -18,6 +18,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 import threading
+import warnings
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libsdp4.so")
 _lock = threading.Lock()
@@ -78,13 +79,23 @@ def lib() -> C.CDLL:
 
 
 def _bind(L) -> None:
-    """Point the native marshalling at the library's entry points."""
+    """Point the native marshalling at the library's entry points.  Without
+    it -- not built, or built for another torch, whose tensors it would
+    misread -- every call takes the general path, which a warning says."""
     global _fast
     try:
-        import torch  # noqa: F401  the extension's libraries come with torch
+        import torch  # the extension's libraries come with torch
     except ImportError:
         return  # addresses only, on the general path
-    from . import _binding
+    try:
+        from . import _binding
+    except ImportError as e:
+        warnings.warn(f"sdp4: no native argument marshalling, calls take longer on the host: {e}", RuntimeWarning)
+        return
+    if _binding.torch_version != torch.__version__:
+        warnings.warn(f"sdp4: native argument marshalling was built for torch {_binding.torch_version}, not "
+                      f"{torch.__version__}, and is not used: calls take longer on the host", RuntimeWarning)
+        return
     _binding.bind(*[C.cast(getattr(L, "sdp4_" + n), C.c_void_p).value for n in
                     ("qwd_encode", "qwd_decode", "qwd_encode_sym", "qwd_decode_sym", "grad_quant", "grad_quant_sr",
                      "dequant_reduce", "dequant_reduce_sr")])

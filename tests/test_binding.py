@@ -19,6 +19,44 @@ def native():
 N, G = 4096, 128
 
 
+def _unbound(monkeypatch):
+    """sdp4 as before its first call, to be put back after the test."""
+    native()
+    monkeypatch.setattr(sdp4, "_lib", None)
+    monkeypatch.setattr(sdp4, "_fast", None)
+
+
+def _takes_the_general_path():
+    L = sdp4.lib()
+    assert sdp4._fast is None and sdp4.sdp4_num_groups(N, G) == N // G
+    assert sdp4.chunk_addresses(None, None, 1, 0, 0) is None
+    with pytest.raises(sdp4.Sdp4Error) as e:                                      # an unknown code width, no HIP call
+        sdp4.sdp4_grad_quant(1 << 20, 5, 0, G, 1 << 21, 1 << 22, N, 0)
+    assert e.value.status == sdp4.EINVAL and L is sdp4.lib()
+
+
+@pytest.mark.cpu_only
+def test_library_without_its_binding_says_so_and_works(monkeypatch):
+    import sys
+
+    import paper_2410_15526_amd as package
+    _unbound(monkeypatch)
+    monkeypatch.delattr(package, "_binding")
+    monkeypatch.setitem(sys.modules, "paper_2410_15526_amd._binding", None)       # its import raises ImportError
+    with pytest.warns(RuntimeWarning, match="no native argument marshalling"):
+        _takes_the_general_path()
+
+
+@pytest.mark.cpu_only
+def test_binding_of_another_torch_is_not_used(monkeypatch):
+    f = native()
+    assert f.torch_version == torch.__version__
+    _unbound(monkeypatch)
+    monkeypatch.setattr(f, "torch_version", "1.0")
+    with pytest.warns(RuntimeWarning, match="built for torch 1.0"):
+        _takes_the_general_path()
+
+
 @pytest.mark.cpu_only
 def test_leaves_what_is_not_on_a_gpu_or_not_ordinary():
     f = native()
