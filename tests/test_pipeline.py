@@ -1,0 +1,52 @@
+"""HotPath's host logic: which chunks its reductions are given."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2410_15526_amd import sdp4  # noqa: E402
+from paper_2410_15526_amd.pipeline import HotPath  # noqa: E402
+
+
+@pytest.fixture
+def calls(monkeypatch):
+    """The chunks of each reduction, with addresses offered for every plain buffer; nothing is launched."""
+    got = []
+    monkeypatch.setattr(sdp4, "chunk_addresses", lambda *a: (["addresses"], ["addresses"]))
+    for name in ("sdp4_dequant_reduce", "sdp4_dequant_reduce_sr"):
+        monkeypatch.setattr(sdp4, name, lambda codes, scales, *a, **k: got.append((codes, scales)))
+    return got
+
+
+def reductions(h):
+    h.reduce_intra()
+    h.reduce_inter()
+    h.reduce_intra_sr()
+
+
+def make(cls):
+    return cls(1 << 14, 64, 64, 4, 2, 128, "f32", device="cpu")
+
+
+def test_own_buffers_go_by_address(calls):
+    reductions(make(HotPath))
+    assert calls == [(["addresses"], ["addresses"])] * 3
+
+
+def test_chunks_of_a_subclass_are_used(calls):
+    class Received(HotPath):
+        def intra_chunks(self, bits=8):
+            return ["c8"] * self.P, ["s8"] * self.P
+
+        def inter_chunks(self):
+            return ["c4"] * self.Q, ["s4"] * self.Q
+
+    reductions(make(Received))
+    assert calls == [(["c8"] * 4, ["s8"] * 4), (["c4"] * 2, ["s4"] * 2), (["c8"] * 4, ["s8"] * 4)]
+
+
+def test_chunks_set_on_an_object_are_used(calls):
+    h = make(HotPath)
+    h.intra_chunks = lambda bits=8: ("c8", "s8")
+    h.inter_chunks = lambda: ("c4", "s4")
+    reductions(h)
+    assert calls == [("c8", "s8"), ("c4", "s4"), ("c8", "s8")]
