@@ -642,15 +642,14 @@ constexpr uint32_t kAllPeers = peer_range(1, 16);
 // 16 peers have instantiations of their own, without tests of P between the
 // loads (2^27 input elements, against the guarded form on the same box: 4 to 4
 // bits 18.6 -> 17.5 us with 4 peers and 18.0 -> 16.0 with 16, 8 to 4 bits of
-// small chunks 3.6 -> 3.2); other counts, and with GUARDED whatever `guarded`
-// asks for, take the guarded one.
-template <template <int, bool> class K, uint32_t PEERS, bool GUARDED, class Go>
-int with_peers(int P, bool guarded, Go go)
+// small chunks 3.6 -> 3.2); other counts take the guarded one of 16.
+template <template <int, bool> class K, uint32_t PEERS, class Go>
+int with_peers(int P, Go go)
 {
     const auto exact = [&](auto count, int &rc) {
         constexpr int N = decltype(count)::value;
         if constexpr (PEERS >> N & 1) {
-            if (P == N && !guarded) {
+            if (P == N) {
                 rc = go(K<N, true>::get());
                 return true;
             }
@@ -664,15 +663,24 @@ int with_peers(int P, bool guarded, Go go)
         exact(std::integral_constant<int, 7>{}, rc) || exact(std::integral_constant<int, 8>{}, rc) ||
         exact(std::integral_constant<int, 16>{}, rc))
         return rc;
-    if constexpr (GUARDED && (PEERS & peer_range(1, 4))) {
+    if constexpr (PEERS & peer_range(9, 15))
+        return go(K<16, false>::get());
+    return 1; // not reached: P is in PEERS
+}
+
+// The same with the guarded kernels only, of up to 4, 8 or 16 peers.
+template <template <int, bool> class K, uint32_t PEERS, class Go>
+int with_guarded_peers(int P, Go go)
+{
+    if constexpr (PEERS & peer_range(1, 4)) {
         if (P <= 4)
             return go(K<4, false>::get());
     }
-    if constexpr (GUARDED && (PEERS & peer_range(5, 8))) {
+    if constexpr (PEERS & peer_range(5, 8)) {
         if (P <= 8)
             return go(K<8, false>::get());
     }
-    if constexpr (PEERS & (GUARDED ? peer_range(9, 16) : peer_range(9, 15)))
+    if constexpr (PEERS & peer_range(9, 16))
         return go(K<16, false>::get());
     return 1; // not reached: P is in PEERS
 }
@@ -695,9 +703,12 @@ int requant(const PeerTable &peers, int P, int64_t n, int gs, int cap, uint8_t *
     const auto go = [&](auto kernel) {
         return launch_tiles<E, WPB>(kernel, n, cap, s, peers, P, n, gs, out_codes, out_scales, out_f32, seed, offset);
     };
-    if ((1 << gs) > kWave * E)
-        return with_peers<Requant<BITS_IN, BITS_OUT, E, WPB, SR, true>::template Kernel, PEERS, true>(P, out_f32, go);
-    return with_peers<Requant<BITS_IN, BITS_OUT, E, WPB, SR, false>::template Kernel, PEERS, true>(P, out_f32, go);
+    const auto pick = [&](auto wide) {
+        using R = Requant<BITS_IN, BITS_OUT, E, WPB, SR, decltype(wide)::value>;
+        return out_f32 ? with_guarded_peers<R::template Kernel, PEERS>(P, go)
+                       : with_peers<R::template Kernel, PEERS>(P, go);
+    };
+    return (1 << gs) > kWave * E ? pick(std::true_type{}) : pick(std::false_type{});
 }
 
 // 8-bit messages: 16 elements per lane, one 16-byte chunk per peer; a wave
@@ -754,41 +765,86 @@ struct ReduceToF32 {
     };
 };
 
-// Dequantize-reduce to float32: 16 elements per lane (4 KiB written per wave).
-// 8-bit messages in 4-wave blocks, <= 5 per CU for one peer, <= 4 for more (us,
-// 2^29 input elements, <= 4 / 5 / 6 / 8 per CU: P = 2 243 / 247 / 261 / 281; P = 1
-// 2 to 5 % faster at 5).  4-bit messages: from 8 peers on 8-wave blocks <= 3 for
-// all but short launches (P = 8, chunks of 2^24 / 50.8M 24.9 / 67.7, 4-wave <= 4
-// 26.9 / 71.4; P = 16, 2^23 20.2 and 24.3); fewer peers in 4-wave blocks, <= 4
-// from 4 peers on, <= 5 below (2^29 input elements, P = 2 <= 4 / 5 / 6 / 8 216 /
-// 208 / 212 / 242), but 4 peers with chunks of 2^24 and more in 2-wave blocks <= 8
-// (50.8M 50.4, 4-wave <= 4 52.0).  32 elements per lane, 8 KiB written per wave,
-// are slower in general (P = 4, 2^29 133, with 16 124; 2^21 4.5 and 4.1) and
-// faster for 3 and 4 peers while the result is of the order of the last-level
-// caches (28 to 48 MB: P = 4, 7340032 / 2^23 / 9437184 7.8 / 8.9 / 10.8, with 16
-// per lane 9.5 / 11.3 / 12.4; 6291456 and 12582912 the same either way), and
-// for 5 to 7 peers from there on (P = 5, 2^23 10.9, with 16 12.2).
+// Bytes that a reduction to float32 reads and writes from which it no longer
+// runs within the L2 caches (8 of 4 MB), with a transform of NB points: the more
+// arithmetic, the later.
+template <int NB>
+constexpr int64_t kSpill = int64_t(NB == 0 ? 25 : NB <= 64 ? 31 : NB <= 256 ? 33 : 38) << 20;
+
+// Dequantize-reduce to float32: 16 elements per lane (4 KiB written per wave) in
+// general.  us with groups of 128, each pass on other inputs; M = 2^20 elements of
+// a chunk, MB = 2^20 bytes read and written.
+//
+// 8-bit messages in 4-wave blocks, <= 5 per CU for one peer, <= 4 for more (2^29
+// input elements, <= 4 / 5 / 6 / 8 per CU: P = 2 243 / 247 / 261 / 281; P = 1 2 to
+// 5 % faster at 5).  From kSpill (36 MB for 3 peers) to 49 MB, 3 to 8 peers, 6 and
+// more up to 4 M, take the guarded kernels: their loads go out one by one, each
+// after its peer's pointer, which the caches serve better there and worse elsewhere
+// (guarded and exact without a transform / with 256 points: P = 4, 4 M 5.8 and 6.8 /
+// 6.1 and 6.1, 5 M 7.1 and 8.3 / 7.0 and 8.1; P = 5, 4 M 6.7 and 7.9 / 7.0 and 8.1;
+// P = 8, 3 M 7.2 and 7.6 / 7.6 and 7.6; P = 3, 6 M 7.6 and 8.8 / 7.0 and 8.7; outside,
+// P = 4, 3 M 4.95 and 4.85 / 5.5 and 4.9; P = 8, 4.5 M 11.9 and 10.8 / 12.3 and 11.0).
+//
+// 4-bit messages:
+//   1 and 2 peers: 4-wave blocks, uncapped up to 20 M with at most 256 points (P = 1,
+//     12 M, no transform 9.7, <= 5 per CU 11.1; 1024 points, 11 M 11.2, <= 5 10.3),
+//     above <= 6 and <= 5 (P = 1, 64 M <= 5 / 6 51.9 / 49.8; 2^29 input elements, P = 2
+//     <= 4 / 5 / 6 / 8 216 / 208 / 212 / 242).
+//   3 to 8 peers from kSpill (5 MB more for 3) on, without a transform also 2 (11 MB
+//     more): 32 elements per lane, 8 KiB written per wave, <= 4 per CU, up to 12 M for
+//     2 to 4 peers, 6.5 M for 8 (9 M with 512 points and more) (16 and 32 per lane, no
+//     transform: P = 2, 8 M 8.4 and 7.1; P = 4, 5.5 M 8.05 and 5.96; P = 6, 4.5 M 8.0
+//     and 6.3; P = 8, 4 M 7.9 and 6.6; 256 points: P = 5, 5.5 M 8.5 and 7.1; below
+//     kSpill, 256 points, P = 4, 3.5 M 5.1 and 5.5; P = 4, 2^27 124 and 133).  9 to 15
+//     peers the same from 5 M, with a transform 6.5 M, to 9 M (P = 11, 7 M, no transform
+//     / 256 points 14.4 / 15.3, 8-wave blocks 15.8 / 15.8).  While the result is of the
+//     order of the L2s, 6.5 to 8 M, from 4 peers on without a transform in the guarded
+//     form (P = 4, 7.5 M 8.2, exact 9.2; P = 7, 7 M 9.5 and 12.0, 9 M 14.6 and 14.7).
+//   8 and more peers beyond that, from 6 M on: 8-wave blocks <= 3 (P = 8, 2^24 / 50.8M
+//     24.9 / 67.7, 4-wave <= 4 26.9 / 71.4; P = 16, 2^23 20.2 and 24.3; below, P = 16,
+//     2.7 M 9.6 and 4-wave 8.5, P = 11, 5 M 11.3 and 10.6).
+//   4 peers with chunks of 2^24 and more: 2-wave blocks <= 8 (2^25 / 45969408 / 2^26
+//     36.1 / 44.5 / 65.6, 4-wave <= 4 36.7 / 44.5 / 67.9).
+//   The rest: 4-wave blocks, <= 4 from 4 peers on, <= 5 for 3.
 template <int BITS_IN, int NB>
 int reduce_to_f32(const PeerTable &peers, int P, int64_t n, int gs, float cn, float out_scale, float *out_f32,
                       hipStream_t s)
 {
-    const auto go = [&](auto shape, int cap) {
+    const auto go = [&](auto shape, int cap, auto guarded) {
         using S = decltype(shape);
-        return with_peers<ReduceToF32<BITS_IN, NB, S::E, S::WPB>::template Kernel, S::PEERS, false>(
-            P, false, [&](auto kernel) {
-                return launch_tiles<S::E, S::WPB>(kernel, n, cap, s, peers, P, n, gs, cn, out_scale, out_f32);
-            });
+        using R = ReduceToF32<BITS_IN, NB, S::E, S::WPB>;
+        const auto run = [&](auto kernel) {
+            return launch_tiles<S::E, S::WPB>(kernel, n, cap, s, peers, P, n, gs, cn, out_scale, out_f32);
+        };
+        if constexpr (decltype(guarded)::value)
+            return with_guarded_peers<R::template Kernel, S::PEERS>(P, run);
+        else
+            return with_peers<R::template Kernel, S::PEERS>(P, run);
     };
+    constexpr std::true_type guarded{};
+    constexpr std::false_type exact{};
+    constexpr int64_t M = int64_t(1) << 20;
+    const int64_t bytes = n * (8 * 4 + P * BITS_IN) / 8;
     if constexpr (BITS_IN == 4) {
-        if (P >= 8 && n >= (int64_t(1) << 21))
-            return go(Shape<16, 8, peer_range(8, 16)>{}, 3);
-        if (P >= 3 && P < 8 && n >= (int64_t(7) << 20) && (P > 4 || n < (int64_t(12) << 20)))
-            return go(Shape<32, 4, peer_range(3, 7)>{}, 4);
-        if (P == 4 && n >= (int64_t(1) << 24))
-            return go(Shape<16, 2, 1u << 4>{}, 8);
-        return go(Shape<16, 4, kAllPeers>{}, P >= 4 ? 4 : 5);
+        const int64_t from = kSpill<NB> + (P == 2 ? 11 * M : P == 3 ? 5 * M : 0);
+        if (P >= (NB == 0 ? 2 : 3) && (P <= 8 ? bytes >= from : P < 16 && n > (NB == 0 ? 5 * M : 13 * M / 2))) {
+            if constexpr (NB == 0) {
+                if (P >= 4 && P <= 8 && n >= 13 * M / 2 && n <= 8 * M)
+                    return go(Shape<32, 4, peer_range(4, 8)>{}, 4, guarded);
+            }
+            if (P <= 4 ? n < 12 * M : P < 8 || (P == 8 ? n < (NB > 256 ? 9 * M : 13 * M / 2) : n <= 9 * M))
+                return go(Shape<32, 4, peer_range(NB == 0 ? 2 : 3, 15)>{}, 4, exact);
+        }
+        if (P >= 8 && n >= 6 * M)
+            return go(Shape<16, 8, peer_range(8, 16)>{}, 3, exact);
+        if (P == 4 && n >= 16 * M)
+            return go(Shape<16, 2, 1u << 4>{}, 8, exact);
+        return go(Shape<16, 4, kAllPeers>{},
+                  P >= 4 ? 4 : P == 3 ? 5 : NB <= 256 && n <= 20 * M ? kUncapped : P == 1 ? 6 : 5, exact);
     } else {
-        return go(Shape<16, 4, kAllPeers>{}, P >= 2 ? 4 : 5);
+        if (P >= 3 && P <= 8 && bytes >= (P == 3 ? 36 * M : kSpill<NB>) && bytes <= 49 * M && (P <= 5 || n <= 4 * M))
+            return go(Shape<16, 4, peer_range(3, 8)>{}, 4, guarded);
+        return go(Shape<16, 4, kAllPeers>{}, P >= 2 ? 4 : 5, exact);
     }
 }
 

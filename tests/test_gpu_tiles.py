@@ -223,20 +223,33 @@ def test_requant_of_8_peers_at_its_block_shape_switch():
         assert t.equal(oc, wc.repeat(reps)[:m // 2]) and t.equal(osc, ws.repeat(reps)[:m // group])
 
 
-# Chunk sizes on either side of every switch of the float32 reduction of 4-bit messages: 2^21 elements for
-# 8 and more peers, 7 and 12 times 2^20 for 3 to 7, 2^24 for 4.
-@pytest.mark.parametrize("P,n", [(16, (1 << 21) - 256), (9, 1 << 21), (3, (7 << 20) - 256), (3, 7 << 20), (4, 12 << 20),
-                                 (5, (7 << 20) + 256), (4, (1 << 24) - 256), (4, (1 << 24) + 256), (2, 7 << 20)])
-@pytest.mark.parametrize("group,block", [(128, 256), (32, 0)])
-def test_4_bit_reduction_to_f32_around_its_shape_switches(P, n, group, block):
-    say(f"reduce f32 P={P} n={n} group={group} block={block}")
-    msgs = _messages(1, 1 << 20, 4, group, P + n)
-    c = [np.resize(np.roll(msgs[0][0], 16 * group * p), n // 2) for p in range(P)]
-    s = [np.resize(np.roll(msgs[0][1], p), n // group) for p in range(P)]
+# Chunk sizes on either side of every switch of the float32 reductions, most of them bytes read and written
+# (25, 31, 33 or 38 MB by the transform's points), with and without a transform that spans lanes.
+M = 1 << 20
+F32_4_BIT = [(0, 4, 4368896), (0, 4, 4369152), (0, 4, 13 * M // 2 - 256), (0, 4, 13 * M // 2), (0, 7, 8 * M),
+             (0, 7, 8 * M + 256), (0, 8, 25 * M // 8 - 256), (0, 8, 25 * M // 8), (0, 8, 13 * M // 2), (0, 8, 8 * M + 256),
+             (0, 3, 5719552), (0, 3, 5719808), (0, 3, 12 * M), (0, 11, 5 * M), (0, 11, 5 * M + 256), (0, 9, 9 * M + 256),
+             (0, 16, 6 * M - 256), (0, 16, 6 * M), (0, 2, 20 * M), (0, 1, 20 * M + 256), (32, 5, 5000960), (32, 5, 5001216),
+             (0, 2, 36 * M // 5), (0, 2, 36 * M // 5 + 256), (0, 2, 12 * M), (64, 6, 6 * M), (256, 7, 4613632), (256, 7, 4613888), (256, 4, 12 * M - 256), (256, 4, 12 * M),
+             (256, 4, 16 * M - 256), (256, 4, 16 * M), (256, 8, 13 * M // 2 - 256), (256, 8, 13 * M // 2),
+             (256, 11, 13 * M // 2 + 256), (2, 4, 7 * M), (512, 6, 6 * M), (1024, 6, 5691392), (1024, 6, 5692416),
+             (1024, 1, 11 * M), (1024, 8, 7 * M), (512, 8, 9 * M)]
+F32_8_BIT = [(0, 4, 25 * M // 8 - 256), (0, 4, 25 * M // 8), (0, 4, 49 * M // 8), (0, 4, 49 * M // 8 + 256), (0, 3, 5392896),
+             (0, 3, 5393152), (0, 8, 4 * M), (0, 8, 4 * M + 256), (256, 5, 4 * M), (1024, 5, 38 * M // 8), (32, 6, 13 * M // 4)]
+
+
+@pytest.mark.parametrize("bits,block,P,n", [(4, *c) for c in F32_4_BIT] + [(8, *c) for c in F32_8_BIT])
+def test_reduction_to_f32_around_its_shape_switches(bits, block, P, n):
+    group = 32 if block == 2 else 128
+    n = n // max(block, group) * max(block, group)
+    say(f"reduce f32 bits={bits} P={P} n={n} group={group} block={block}")
+    codes, scales = _messages(1, M, bits, group, P + n)[0]
+    c = [np.resize(np.roll(codes, 16 * group * p), n * bits // 8) for p in range(P)]
+    s = [np.resize(np.roll(scales, p), n // group) for p in range(P)]
     out = empty(n, "f32")
-    sdp4.sdp4_dequant_reduce([dev(x) for x in c], [dev(x) for x in s], n, 4, group, 0, block, 0.25, out_f32=out)
+    sdp4.sdp4_dequant_reduce([dev(x) for x in c], [dev(x) for x in s], n, bits, group, 0, block, 0.25, out_f32=out)
     sync()
-    ref = oracle.dequant_reduce(c, s, n, 4, group, 0, block, 0.25)
+    ref = oracle.dequant_reduce(c, s, n, bits, group, 0, block, 0.25)
     check_f32(host(out), ref["f32"])
 
 
