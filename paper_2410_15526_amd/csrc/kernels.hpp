@@ -685,9 +685,6 @@ int with_guarded_peers(int P, Go go)
     return 1; // not reached: P is in PEERS
 }
 
-// Re-quantizing dequantize-reduce of PEERS peers, in blocks of WPB waves, <= cap
-// per CU; groups beyond a wave tile are shared by the waves of a block.
-// The optional float32 copy of the sums is the guarded kernels'.
 template <int BITS_IN, int BITS_OUT, int E, int WPB, bool SR, bool WIDE>
 struct Requant {
     template <int PMAX, bool EXACT>
@@ -696,40 +693,46 @@ struct Requant {
     };
 };
 
-template <int BITS_IN, int BITS_OUT, int E, int WPB, bool SR, uint32_t PEERS>
-int requant(const PeerTable &peers, int P, int64_t n, int gs, int cap, uint8_t *out_codes, float *out_scales,
-            float *out_f32, hipStream_t s, uint64_t seed, uint64_t offset)
-{
-    const auto go = [&](auto kernel) {
-        return launch_tiles<E, WPB>(kernel, n, cap, s, peers, P, n, gs, out_codes, out_scales, out_f32, seed, offset);
-    };
-    const auto pick = [&](auto wide) {
-        using R = Requant<BITS_IN, BITS_OUT, E, WPB, SR, decltype(wide)::value>;
-        return out_f32 ? with_guarded_peers<R::template Kernel, PEERS>(P, go)
-                       : with_peers<R::template Kernel, PEERS>(P, go);
-    };
-    return (1 << gs) > kWave * E ? pick(std::true_type{}) : pick(std::false_type{});
-}
-
+// Shapes of the re-quantizing dequantize-reduce (us; M = 2^20 elements of a chunk).
+//
 // 8-bit messages: 16 elements per lane, one 16-byte chunk per peer; a wave
 // keeps P KiB in flight.  1 and 2 peers: 4-wave blocks, <= 8 per CU.  16 peers,
-// and short launches of 4 and 8: 4-wave blocks <= 4, which spread better.
-// Others: 8-wave blocks <= 3, or <= 2 for 8 peers with chunks of 2^26 elements
-// and more; they suffer less where the chunks of the peers lie a large power
-// of two apart (as those of power-of-two widths do) and their rows meet in
-// the same memory banks.  us, 8 to 4 bits, 4-wave <= 4 (<= 8 up to 3 peers)
+// 4 and 8 in short launches and 4 in large ones: 4-wave blocks <= 4, which spread
+// better.  4 and 8 peers otherwise: 8-wave blocks <= 3, or <= 2 for 8 peers with
+// chunks of 64 M and more; they suffer less where the chunks of the peers lie a
+// large power of two apart (as those of power-of-two widths do) and their rows
+// meet in the same memory banks.  8 to 4 bits, 4-wave <= 4 (<= 8 up to 3 peers)
 // against 8-wave <= 3:
 //   P = 8, chunks of 2^24 29.2 / 26.7, 2^24 + 12288 25.0 / 25.1, 5 * 2^22
 //     33.7 / 32.2, 26214400 37.4 / 37.9, 2^19 3.1 / 3.8; 105M and 203M 146.9 /
 //     285.6, 8-wave <= 2 140.4 / 277.5
 //   P = 4, 2^25 28.4 / 27.1, 2^25 + 12288 26.1 / 26.0; 2^27 101.6 / 103 or more
-//   P = 3, 60M 105 / 99;  P = 2, 134M 107 / 117;  P = 16, 2^23 28.3 / 29.0,
-//     2^23 + 6144 25.0 / 26.4
+//   P = 2, 134M 107 / 117;  P = 16, 2^23 28.3 / 29.0, 2^23 + 6144 25.0 / 26.4, 2^24
+//     56.3 / 54.2, 11.5M 34.1 / 35.0
+// 3, 5 to 7 and 9 to 15 peers: 8-wave blocks <= 3 at every size, for the large
+// launches (P = 3 / 6, 64 M 41.6 / 32 M 40.1 and 38.5 / 38.6; 16 M 12.7 / 20.9 and
+// 11.5 / 20.5); from 2 to 10 M both shapes are within 5 % either way, and launches
+// of 1 M and less are the slower for it (P = 3 / 6, 1 M 2.9 / 3.15 and 3.2 / 3.65).
+//
 // 4-bit messages: 4-wave blocks, 32 elements per lane (a 16-byte chunk per
 // peer) <= 6 per CU for the large launches of up to 7 peers, else 16 per lane
-// <= 8, or, from 8 peers and 2^22 elements on, in 8-wave blocks <= 4 (2^29 input
+// <= 8, or, from 8 peers and 4 M on, in 8-wave blocks <= 4 (2^29 input
 // elements, P = 4 56.3 against 59.7 with 16 per lane; P = 8, chunks of 2^24 /
 // 2^24 + 12288 / 50.8M 4-wave 17.8 / 15.0 / 43.7, 8-wave 15.6 / 15.7 / 40.4).
+//
+// With the float32 copy four fifths and more of a launch's writes are the copy, and
+// other shapes serve them better.  4-bit messages of 4 M and more: 1 peer, and up
+// to 9 M up to 8 peers, 32 per lane <= 6 (P = 8, 5 M 9.15, 8-wave 16 per lane 10.7);
+// 2 to 7 peers then 16 per lane in 4-wave blocks <= 6, for 2 uncapped (P = 4, 11 M 15.3,
+// 32 per lane 15.9; P = 6, 12 M 18.1 and 20.3; P = 2, 12 M 12.45, <= 6 13.9) and from 16 M on in 8-wave blocks <= 3 (P = 2 / 4,
+// 128 M 114.8 / 138.5, 4-wave 116.5 / 141, 32 per lane 131.9 / 155.9; 1 peer 114.7, 32
+// per lane 110.5).  8-bit messages of 16 peers and 4 M or more: 8-wave blocks <= 3
+// (8 / 16 M 34.2 / 66.6, 4-wave 36.6 / 71.7).
+//
+// Stochastic rounding takes the same shapes.  Its kernels are bound by instructions,
+// and a cap does not move them (8 to 4 bits, as here and uncapped: P = 2, 128 M 68.7
+// and 68.5; P = 4, 44 M 35.0 and 36.6; P = 8, 32 M 51.7 and 51.5; P = 16, 12 M 40.5
+// and 40.3; 4 to 4 bits P = 4, 128 M 79.5 and 76.8, P = 8, 44 M 43.4 and 43.0).
 template <int E_, int WPB_, uint32_t PEERS_>
 struct Shape { // elements per lane, waves per block, peer counts that take it
     static constexpr int E = E_, WPB = WPB_;
@@ -740,21 +743,45 @@ template <int BITS_IN, int BITS_OUT, bool SR>
 int requant_for(const PeerTable &peers, int P, int64_t n, int gs, uint8_t *out_codes, float *out_scales, float *out_f32,
                 hipStream_t s, uint64_t seed, uint64_t offset)
 {
-    const auto go = [&](auto shape, int cap) {
+    // groups beyond a wave tile are shared by the waves of a block
+    const auto go = [&](auto shape, int cap, auto guarded) {
         using S = decltype(shape);
-        return requant<BITS_IN, BITS_OUT, S::E, S::WPB, SR, S::PEERS>(peers, P, n, gs, cap, out_codes, out_scales, out_f32,
-                                                                    s, seed, offset);
+        const auto run = [&](auto kernel) {
+            return launch_tiles<S::E, S::WPB>(kernel, n, cap, s, peers, P, n, gs, out_codes, out_scales, out_f32, seed,
+                                              offset);
+        };
+        const auto pick = [&](auto wide) {
+            using R = Requant<BITS_IN, BITS_OUT, S::E, S::WPB, SR, decltype(wide)::value>;
+            if constexpr (decltype(guarded)::value)
+                return with_guarded_peers<R::template Kernel, S::PEERS>(P, run);
+            else
+                return with_peers<R::template Kernel, S::PEERS>(P, run);
+        };
+        return (1 << gs) > kWave * S::E ? pick(std::true_type{}) : pick(std::false_type{});
     };
-    if constexpr (BITS_IN == 4) {
-        if (n < (int64_t(1) << 22))
-            return go(Shape<16, 4, kAllPeers>{}, 8);
-        return P < 8 ? go(Shape<32, 4, peer_range(1, 7)>{}, 6) : go(Shape<16, 8, peer_range(8, 16)>{}, 4);
-    } else {
-        const bool large = n >= (int64_t(1) << 26), small = n < (int64_t(1) << 23);
-        if (P & (P - 1) || (P == 8 && !small) || (P == 4 && !small && !large))
-            return go(Shape<16, 8, peer_range(3, 15)>{}, P == 8 && large ? 2 : 3);
-        return go(Shape<16, 4, (1u << 1 | 1u << 2 | 1u << 4 | 1u << 8 | 1u << 16)>{}, P >= 4 ? 4 : 8);
-    }
+    constexpr int64_t M = int64_t(1) << 20;
+    const auto shaped = [&](auto f32) {
+        constexpr bool F32 = decltype(f32)::value; // the float32 copy: the guarded kernels
+        if constexpr (BITS_IN == 4) {
+            if (n < 4 * M)
+                return go(Shape<16, 4, kAllPeers>{}, 8, f32);
+            if constexpr (F32) {
+                if (P == 1 || (n <= 9 * M && (P < 8 || (P == 8 && n > 4 * M))))
+                    return go(Shape<32, 4, peer_range(1, 8)>{}, 6, f32);
+                if (P < 8)
+                    return n < 16 * M ? go(Shape<16, 4, kAllPeers>{}, P == 2 ? kUncapped : 6, f32)
+                                      : go(Shape<16, 8, peer_range(2, 16)>{}, 3, f32);
+                return go(Shape<16, 8, peer_range(2, 16)>{}, 4, f32);
+            }
+            return P < 8 ? go(Shape<32, 4, peer_range(1, 7)>{}, 6, f32) : go(Shape<16, 8, peer_range(8, 16)>{}, 4, f32);
+        } else {
+            const bool large = n >= 64 * M, small = n < 8 * M;
+            if (P & (P - 1) || (P == 8 && !small) || (P == 4 && !small && !large) || (F32 && P == 16 && n >= 4 * M))
+                return go(Shape<16, 8, F32 ? peer_range(3, 16) : peer_range(3, 15)>{}, P == 8 && large ? 2 : 3, f32);
+            return go(Shape<16, 4, (1u << 1 | 1u << 2 | 1u << 4 | 1u << 8 | 1u << 16)>{}, P >= 4 ? 4 : 8, f32);
+        }
+    };
+    return out_f32 ? shaped(std::true_type{}) : shaped(std::false_type{});
 }
 
 template <int BITS_IN, int NB, int E, int WPB>

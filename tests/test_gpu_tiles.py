@@ -104,7 +104,7 @@ def _messages(P, n, bits, group, seed):
 
 
 # Every peer count with a kernel of its own and one of each guarded kernel,
-# at block edges; above 2^22 elements 4-bit messages take 32 elements per lane.
+# at block edges of the shapes of small launches.
 @pytest.mark.parametrize("P", [1, 2, 3, 4, 5, 8, 11, 16])
 @pytest.mark.parametrize("bits_in", [4, 8])
 @pytest.mark.parametrize("group,n", [(32, 4096 + 32), (1024, 3 * 4096 - 1024), (2048, 8192 + 2048), (4096, 8192 + 4096)])
@@ -223,9 +223,45 @@ def test_requant_of_8_peers_at_its_block_shape_switch():
         assert t.equal(oc, wc.repeat(reps)[:m // 2]) and t.equal(osc, ws.repeat(reps)[:m // group])
 
 
+M = 1 << 20
+
+
+# Above 4 M elements 4-bit messages of up to 7 peers take 32 elements per lane, of more peers 8-wave blocks; with
+# the float32 copy shapes of their own.  Each size on either side of a switch, with a partial last block.
+@pytest.mark.parametrize("bits_in,P,n", [(4, 1, 4 * M), (4, 3, 4 * M + 8192), (4, 4, 9 * M - 4096), (4, 4, 9 * M),
+                                         (4, 7, 16 * M - 4096), (4, 2, 16 * M), (4, 8, 4 * M), (4, 8, 4 * M + 4096),
+                                         (4, 8, 9 * M), (4, 11, 4 * M + 4096), (4, 16, 4 * M), (8, 16, 4 * M - 4096),
+                                         (8, 16, 4 * M), (8, 11, 4 * M + 4096), (8, 5, 12288), (8, 8, 8 * M + 4096)])
+@pytest.mark.parametrize("group", [32, 4096])
+def test_large_requant_with_and_without_the_float32_copy(bits_in, P, n, group):
+    n += group
+    say(f"requant with copy P={P} in={bits_in} group={group} n={n}")
+    codes, scales = _messages(1, M, bits_in, group, P + n)[0]
+    c = [np.resize(np.roll(codes, 16 * group * p), n * bits_in // 8) for p in range(P)]
+    s = [np.resize(np.roll(scales, p), n // group) for p in range(P)]
+    cd, sd = [dev(x) for x in c], [dev(x) for x in s]
+    for bits_out in (4, 8):
+        for seed in (None, 5):
+            if seed is None:
+                ref = oracle.dequant_reduce(c, s, n, bits_in, group, bits_out)
+            else:
+                ref = oracle.dequant_reduce_sr(c, s, n, bits_in, group, bits_out, seed, 16)
+            for copy in (False, True):
+                oc, osc = empty(n * bits_out // 8, "u8"), empty(n // group, "f32")
+                out = empty(n, "f32") if copy else None
+                if seed is None:
+                    sdp4.sdp4_dequant_reduce(cd, sd, n, bits_in, group, bits_out, out_codes=oc, out_scales=osc, out_f32=out)
+                else:
+                    sdp4.sdp4_dequant_reduce_sr(cd, sd, n, bits_in, group, bits_out, seed, 16, oc, osc, out)
+                sync()
+                assert np.array_equal(host(oc), np.ascontiguousarray(ref["codes"]).view(np.uint8))
+                assert np.array_equal(host(osc), ref["scales"])
+                if copy:
+                    check_f32(host(out), ref["f32"])
+
+
 # Chunk sizes on either side of every switch of the float32 reductions, most of them bytes read and written
 # (25, 31, 33 or 38 MB by the transform's points), with and without a transform that spans lanes.
-M = 1 << 20
 F32_4_BIT = [(0, 4, 4368896), (0, 4, 4369152), (0, 4, 13 * M // 2 - 256), (0, 4, 13 * M // 2), (0, 7, 8 * M),
              (0, 7, 8 * M + 256), (0, 8, 25 * M // 8 - 256), (0, 8, 25 * M // 8), (0, 8, 13 * M // 2), (0, 8, 8 * M + 256),
              (0, 3, 5719552), (0, 3, 5719808), (0, 3, 12 * M), (0, 11, 5 * M), (0, 11, 5 * M + 256), (0, 9, 9 * M + 256),
