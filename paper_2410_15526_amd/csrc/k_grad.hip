@@ -49,11 +49,24 @@ private:
     template <int BITS>
     static int few(const float *x, int64_t n, int gs, float cn, uint8_t *codes, float *scale, hipStream_t s)
     {
-        if (n < (int64_t(1) << 25) && gs <= 9)
+        constexpr int64_t M = int64_t(1) << 20;
+        // Launches about what the L2s hold: 16 per lane in 4-wave blocks, uncapped (5 M elements, against 8 per
+        // lane in 4-wave blocks 5.1 / 5.55 for 4 bits without a transform, 5.75 / 5.95 for 8 bits, and in 8-wave
+        // blocks, for groups of 1024 and more, 5.0 / 5.6 and 5.5 / 6.05; 4 M 4.5 / 4.4, 9 M 8.1 / 8.1 and 9.2 / 9.1,
+        // groups of 1024 8.75 / 9.6).
+        if (n > 4 * M && n <= 9 * M)
+            return quantize<BITS, 16, NB, 4>(x, n, gs, cn, codes, scale, kUncapped, s);
+        if constexpr (BITS == 4) { // beyond, 4-bit codes in groups of 1024 and more, <= 6 (2048, 16 / 20 M 12.9 / 15.8
+            // against 13.95 / 16.6 in 8-wave blocks; 32 M 24.4 and 24.7 with 64 points, 64 M 47.9 and 47.4 without)
+            if (n > 4 * M && n < 32 * M && gs > 9)
+                return quantize<4, 16, NB, 4>(x, n, gs, cn, codes, scale, 6, s);
+        }
+        if (n < 32 * M && gs <= 9)
             return quantize<BITS, 8, NB, 4>(x, n, gs, cn, codes, scale, 8, s);
         if constexpr (BITS == 4 && NB == 256) // 4-bit codes, 2^27 / 2^29 elements: 98.3 / 390, with 8 per lane 99.3 / 396
             return quantize<4, 16, NB, 4>(x, n, gs, cn, codes, scale, 6, s);
-        return quantize<BITS, 8, NB, 8>(x, n, gs, cn, codes, scale, 4, s);
+        else
+            return quantize<BITS, 8, NB, 8>(x, n, gs, cn, codes, scale, 4, s);
     }
 };
 

@@ -178,11 +178,14 @@ def test_stochastic_rounding_of_group_extremes(bits):
         assert np.array_equal(host(scale), want[1])
 
 
-@pytest.mark.parametrize("bits,block", [(8, 256), (4, 0), (4, 128), (4, 256)])
-@pytest.mark.parametrize("extra", [-512, 512])
-def test_grad_quant_around_its_block_shape_switch(bits, block, extra):
-    n, group = (1 << 25) + extra, 512
-    say(f"grad_quant bits={bits} block={block} n={n}")
+@pytest.mark.parametrize("bits,block,group,n", [
+    (b, blk, 512, (1 << 25) + extra) for b, blk in ((8, 256), (4, 0), (4, 128), (4, 256)) for extra in (-512, 512)] + [
+    # 4 to 9 times 2^20 elements, and 4-bit codes in groups of 1024 and more below 2^25
+    (4, 0, 512, 1 << 22), (4, 0, 32, (1 << 22) + 32), (8, 256, 512, 9 << 20), (8, 32, 64, (9 << 20) + 64),
+    (8, 128, 4096, (1 << 22) + 4096), (8, 64, 1024, 9 << 20), (4, 16, 32, 5 << 20), (4, 2, 2048, (1 << 22) + 2048),
+    (4, 0, 2048, (1 << 25) - 2048), (4, 0, 2048, 1 << 25), (4, 64, 1024, (9 << 20) + 1024)])
+def test_grad_quant_around_its_block_shape_switches(bits, block, group, n):
+    say(f"grad_quant bits={bits} block={block} group={group} n={n}")
     x = np.random.default_rng(bits).standard_normal(n, dtype=np.float32)
     codes, scale = empty(n * bits // 8, "u8"), empty(n // group, "f32")
     sdp4.sdp4_grad_quant(dev(x), bits, block, group, codes, scale)
