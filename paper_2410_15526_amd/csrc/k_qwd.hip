@@ -18,14 +18,15 @@ int qwd_encode(const float *w_new, const void *w_prev, bool bf16, bool sym, int6
 
 // 2-wave blocks, <= 8 per CU, 16 elements per lane for bfloat16 weights and 8 for float32: 2 KiB of weights
 // read and written per wave (2^30 elements, <= 6 / 8 / 10 per CU: bfloat16 826 / 751 / 759 us, float32 <= 6 / 7 /
-// 8 / 10 1526 / 1440 / 1408 / 1419).
+// 8 / 10 1526 / 1440 / 1408 / 1419).  Uncapped up to 2^23 elements (uncapped / <= 8: bfloat16, 5.7M 5.4 / 6.0, 7.3M
+// 7.0 / 7.1, 2^24 13.7 / 13.7; float32, 2.9M 5.0 / 5.4, 7.3M 11.3 / 11.6, 2^25 45.4 / 45.5).
 template <bool BF16>
 int qwd_decode(const uint8_t *codes, const float *scale, const float *minv, int64_t n, int gs, void *w_prev, bool sym,
                hipStream_t s)
 {
     constexpr int E = BF16 ? 16 : 8, WPB = 2;
     auto k = sym ? k_qwd_decode<BF16, true, E, WPB> : k_qwd_decode<BF16, false, E, WPB>;
-    return launch_tiles<E, WPB>(k, n, 8, s, codes, scale, minv, n, gs, w_prev);
+    return launch_tiles<E, WPB>(k, n, n <= int64_t(1) << 23 ? kUncapped : 8, s, codes, scale, minv, n, gs, w_prev);
 }
 
 } // namespace
