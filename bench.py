@@ -73,11 +73,12 @@ def _code_tokens(text: str) -> str:
 def source_digest() -> str:
     """Digest of the code that decides what the kernels do on the device:
     the kernels and their launch configuration (not the host-side argument
-    checks of the C ABI), comments and layout ignored."""
+    checks of the C ABI nor the Python binding's marshalling), comments and
+    layout ignored."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2410_15526_amd", "csrc")
     for f in sorted(os.listdir(csrc)):
-        if f == "abi.cpp":
+        if f in ("abi.cpp", "binding.cpp"):
             continue
         with open(os.path.join(csrc, f), encoding="utf-8") as fh:
             h.update(f.encode() + _code_tokens(fh.read()).encode())

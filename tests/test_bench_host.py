@@ -130,3 +130,13 @@ def test_workload_overrides():
                            model_weights=None)
     import synth
     assert bench.workload_from_args(b) is synth.WORKLOADS["c4"]
+
+
+def test_source_digest_leaves_out_the_marshalling_of_the_python_binding(tmp_path, monkeypatch):
+    csrc = tmp_path / "paper_2410_15526_amd" / "csrc"
+    csrc.mkdir(parents=True)
+    (csrc / "kernels.hpp").write_text("a")
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    d0 = bench.source_digest()
+    (csrc / "binding.cpp").write_text("x")
+    assert bench.source_digest() == d0
