@@ -79,8 +79,9 @@ def build_binding(out: str = BINDING) -> str | None:
 
 
 def build(verbose: bool = False, defines=(), out: str | None = None, build_dir: str | None = None) -> str:
-    """Compile and link.  ``defines`` and ``out`` exist for tuning builds
-    (e.g. ``defines=["SDP4_PIPE=0"]``); the default build uses neither."""
+    """Compile and link.  ``out`` and ``build_dir`` put the library (alone) and
+    its objects somewhere else, ``defines`` are macros for hipcc: for builds of
+    changed sources, since the committed ones read no macro."""
     bdir = build_dir or BUILD
     lib = out or LIB
     os.makedirs(bdir, exist_ok=True)

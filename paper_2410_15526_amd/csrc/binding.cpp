@@ -33,8 +33,6 @@ struct Entry {
     decltype(&sdp4_dequant_reduce_sr) dequant_reduce_sr;
 } lib; // set once by bind()
 
-constexpr int64_t kNone = -1; // "n" not given
-
 // Arguments of one call; `ok` turns false at the first that is not ordinary.
 struct Args {
     bool ok = true;

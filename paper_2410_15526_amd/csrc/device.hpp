@@ -485,14 +485,10 @@ SDP4_DEV uint32_t code_bits_sr(float x, float inv, float h, int qmax)
     return (uint32_t)max(i, -qmax);
 }
 
-// signed code e of a chunk array holding `bits`-wide codes
-template <int BITS>
-SDP4_DEV float code_f(const uint32_t *w, int e)
+// signed 8-bit code e of an array of packed codes
+SDP4_DEV float code8_f(const uint32_t *w, int e)
 {
-    if constexpr (BITS == 8)
-        return (float)((int32_t)(w[e >> 2] << (24 - 8 * (e & 3))) >> 24);
-    else
-        return (float)((int32_t)(w[e >> 3] << (28 - 4 * (e & 7))) >> 28);
+    return (float)((int32_t)(w[e >> 2] << (24 - 8 * (e & 3))) >> 24);
 }
 
 // acc[m] = fma(code m, s, acc[m]) for the eight signed 4-bit codes of word w

@@ -6,13 +6,12 @@ namespace sdp4 {
 
 namespace {
 
-template <int WPB, bool WIDE>
-int qwd_encode(const float *w_new, const void *w_prev, bool bf16, bool sym, int64_t n, int gs, uint8_t *codes,
-               float *scale, float *minv, int cap, hipStream_t s)
+template <bool BF16, int WPB, bool WIDE>
+int qwd_encode(const float *w_new, const void *w_prev, bool sym, int64_t n, int gs, uint8_t *codes, float *scale,
+               float *minv, int cap, hipStream_t s)
 {
     constexpr int E = 16;
-    auto k = bf16 ? (sym ? k_qwd_encode<true, true, E, WPB, WIDE> : k_qwd_encode<true, false, E, WPB, WIDE>)
-                  : (sym ? k_qwd_encode<false, true, E, WPB, WIDE> : k_qwd_encode<false, false, E, WPB, WIDE>);
+    auto k = sym ? k_qwd_encode<BF16, true, E, WPB, WIDE> : k_qwd_encode<BF16, false, E, WPB, WIDE>;
     return launch_tiles<E, WPB>(k, n, cap, s, w_new, w_prev, n, gs, codes, scale, minv);
 }
 
@@ -42,12 +41,14 @@ int launch_qwd_encode(const float *w_new, const void *w_prev, bool bf16, bool sy
     if (group > kWave * 16) { // beyond a wave tile; bfloat16 weights <= 4 (groups of 4096 at 1.6e9 1641, <= 3 1664),
         // or large launches whose groups two waves hold as below (2048 at 1.6e9 1699, 4-wave <= 4 1709, <= 3 1718)
         if (bf16 && group == 2048 && n >= (int64_t(1) << 28))
-            return qwd_encode<2, true>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, 6, s);
-        return qwd_encode<4, true>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, bf16 ? 4 : 3, s);
+            return qwd_encode<true, 2, true>(w_new, w_prev, sym, n, gs, codes, scale, minv, 6, s);
+        return bf16 ? qwd_encode<true, 4, true>(w_new, w_prev, sym, n, gs, codes, scale, minv, 4, s)
+                    : qwd_encode<false, 4, true>(w_new, w_prev, sym, n, gs, codes, scale, minv, 3, s);
     }
     if (bf16 && n >= (int64_t(1) << 27))
-        return qwd_encode<2, false>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, 6, s);
-    return qwd_encode<4, false>(w_new, w_prev, bf16, sym, n, gs, codes, scale, minv, 3, s);
+        return qwd_encode<true, 2, false>(w_new, w_prev, sym, n, gs, codes, scale, minv, 6, s);
+    return bf16 ? qwd_encode<true, 4, false>(w_new, w_prev, sym, n, gs, codes, scale, minv, 3, s)
+                : qwd_encode<false, 4, false>(w_new, w_prev, sym, n, gs, codes, scale, minv, 3, s);
 }
 
 int launch_qwd_decode(const uint8_t *codes, const float *scale, const float *minv, int64_t n,

@@ -342,7 +342,7 @@ __global__ __launch_bounds__(kWave * WPB) void k_qwd_decode(
     const uint8_t *__restrict__ codes, const float *__restrict__ scale,
     const float *__restrict__ minv, int64_t n, int gs, void *__restrict__ w_prev)
 {
-    static_assert(E == 8 || E == 16 || E % 32 == 0, "lane slice");
+    static_assert(E == 8 || E == 16, "lane slice");
     using Pl = Place<E, WPB>;
     constexpr int RP = BF16 ? E / 8 : E / 4;   // 16-byte chunks of weights per lane
     constexpr int CWD = E / 8;                 // 32-bit words of codes per lane
@@ -487,7 +487,7 @@ SDP4_DEV void reduce_peers(const PeerTable &peers, int P, int64_t base, uint32_t
             } else {
 #pragma unroll
                 for (int i = 0; i < E; ++i)
-                    acc[i] = __builtin_fmaf(code_f<BITS>(c[j], i), s[j], acc[i]);
+                    acc[i] = __builtin_fmaf(code8_f(c[j], i), s[j], acc[i]);
             }
         }
     }
