@@ -1,12 +1,9 @@
-"""The qWD encoder's phased mode (large launches with bfloat16 model weights:
-loads only in the read part of a clock period, outputs buffered in LDS and
-written in the rest) against the oracle on every element: groups 64..1024,
-both codecs, and a shard whose last wave tile is partial.  Float32 model
-weights stream at every size, so their cases check the streaming encoder at
-the same size.  The
-8-bit K1 and the 4-bit re-quantizing dequantize-reduce (K2: 8- and 4-bit peer
-messages, 2..16 peers) are checked at the same size; they stream without
-phases."""
+"""Every element of launches of 2^26 elements and a partial last block against
+the oracle: the qWD encoder with both codecs, both weight types and groups
+64..1024, the 8-bit K1, and the 4-bit re-quantizing dequantize-reduce (K2: 8-
+and 4-bit peer messages, 2..16 peers).  From 2^26 elements on 8-bit messages
+of 8 peers take fewer blocks per compute unit; the encoder's own switches lie
+higher (test_gpu_tiles.py)."""
 import numpy as np
 import pytest
 
@@ -16,7 +13,7 @@ from tests._gpu import check_codes, check_headers, dev, empty, host, say, torch
 
 pytestmark = pytest.mark.gpu
 
-N = (1 << 26) + 3 * 1024          # above the phased-mode threshold; 3/2 tiles past a whole number
+N = (1 << 26) + 3 * 1024          # three quarters of a 4-wave block of 16 elements per lane past a whole number
 
 
 def inputs(bf16, seed):
@@ -33,8 +30,8 @@ def inputs(bf16, seed):
 
 @pytest.mark.parametrize("bf16,group", [(True, 64), (False, 64), (True, 128), (True, 256), (False, 256), (True, 512),
                                         (True, 1024), (False, 1024)])
-def test_phased_asymmetric_encode_matches_oracle(bf16, group):
-    say(f"phased qwd encode bf16={bf16} group={group} n={N}")
+def test_large_asymmetric_encode_matches_oracle(bf16, group):
+    say(f"large qwd encode bf16={bf16} group={group} n={N}")
     new, prev = inputs(bf16, group)
     codes, scale, minv = empty(N // 2, "u8"), empty(N // group, "f32"), empty(N // group, "f32")
     sdp4.sdp4_qwd_encode(dev(new), dev(prev), group, codes, scale, minv)
@@ -46,8 +43,8 @@ def test_phased_asymmetric_encode_matches_oracle(bf16, group):
 
 
 @pytest.mark.parametrize("bf16,group", [(True, 64), (True, 128), (False, 512)])
-def test_phased_symmetric_encode_matches_oracle(bf16, group):
-    say(f"phased qwd encode sym bf16={bf16} group={group} n={N}")
+def test_large_symmetric_encode_matches_oracle(bf16, group):
+    say(f"large qwd encode sym bf16={bf16} group={group} n={N}")
     new, prev = inputs(bf16, 7 * group)
     codes, scale = empty(N // 2, "u8"), empty(N // group, "f32")
     sdp4.sdp4_qwd_encode_sym(dev(new), dev(prev), group, codes, scale)

@@ -32,10 +32,9 @@ def outputs(hp):
 
 @pytest.mark.parametrize("name,n", [("c1", None), ("c5", 1 << 26)])
 def test_step_replayed_from_a_hip_graph(name, n):
-    """c1: the tiny shard (streaming kernels).  c5 scaled to 2^26 elements:
-    bfloat16 model weights and groups of 128, so the encoder runs in its
-    clock-phased mode (launches of at least 2^26 elements), whose period the
-    host computes from the device's wall-clock rate at capture time."""
+    """c1: the tiny shard, whose launches take no cap on resident blocks.  c5
+    scaled to 2^26 elements, bfloat16 model weights: larger launches, whose
+    reserved LDS and block shapes are recorded with them."""
     t = torch()
     say(f"graph capture of one step: {name} n={n}")
     hp = make_path(name, n)

@@ -178,6 +178,23 @@ def test_stochastic_rounding_of_group_extremes(bits):
         assert np.array_equal(host(scale), want[1])
 
 
+@pytest.mark.parametrize("bits,top", [(8, 127.0), (4, 7.0)])
+def test_stochastic_rounding_of_negative_denormals(bits, top):
+    """A product that is a negative denormal rounds down to -1 where the uniform is 0 (17 of these elements), and
+    would to 0 if the conversion flushed it."""
+    group, n = 32, 1 << 20
+    say(f"sr denormals bits={bits}")
+    x = np.full(n, -1e-41, np.float32)
+    x[::group] = top                                                       # inverse scale 1
+    codes, scale = empty(n * bits // 8, "u8"), empty(n // group, "f32")
+    sdp4.sdp4_grad_quant_sr(dev(x), bits, 0, group, 0, 0, codes, scale)
+    sync()
+    want = oracle.grad_quant_sr(x, bits, 0, group, 0, 0)
+    w = np.ascontiguousarray(want[0]).view(np.uint8)
+    assert np.sum(w == 0xFF) + (np.sum(w & 15 == 15) + np.sum(w >> 4 == 15) if bits == 4 else 0) == 17
+    assert np.array_equal(host(codes), w) and np.array_equal(host(scale), want[1])
+
+
 @pytest.mark.parametrize("bits,block,group,n", [
     (b, blk, 512, (1 << 25) + extra) for b, blk in ((8, 256), (4, 0), (4, 128), (4, 256)) for extra in (-512, 512)] + [
     # 4 to 9 times 2^20 elements, and 4-bit codes in groups of 1024 and more below 2^25
