@@ -472,10 +472,11 @@ SDP4_DEV void sr_uniforms(uint64_t seed, uint64_t e0, float (&h)[E])
 // stays below qmax + 1 and only the lower end needs the clamp (-qmax - ulp
 // with u = 0).  Five instructions per element where scaling u, adding,
 // floor, a two-sided clamp and the magic addition took seven; with bitop3 the
-// rounded K1 (block 256) went from 34 to 28 instructions per element.  It is
-// bound by them: 2^27 elements, block 256, 8 / 4 bits 111.3 / 108.2 us ->
-// 106.2 / 99.8; re-quantizing 8 and 4 to 4 bits, P = 4, 28.8 / 26.3 -> 27.3 /
-// 22.4.
+// rounded K1 (block 256, 8 bits) went from 33.9 to 26.0 instructions per element
+// by the counters, which keep the vector units busy throughout: it is bound by
+// them (in the kernels of the time, which looped over tiles: 2^27 elements,
+// block 256, 8 / 4 bits 111.3 / 108.2 us -> 106.2 / 99.8; re-quantizing 8 and 4
+// to 4 bits, P = 4, 28.8 / 26.3 -> 27.3 / 22.4).
 SDP4_DEV uint32_t code_bits_sr(float x, float inv, float h, int qmax)
 {
     const float v = x * inv;
@@ -498,9 +499,11 @@ SDP4_DEV float code8_f(const uint32_t *w, int e)
 // 1152 + 16 code (bits 4-7), from which one packed operation recovers the
 // code; the mixed-precision fma widens it exactly, so every fma has the same
 // operands as after an integer extract and conversion.  What bounds the
-// 4-bit reductions is vector instructions (3 per element and peer that way
-// against 29 available per element at HBM rate with 8 peers); this takes 2.1.
-// Re-quantizing 4 to 4 bits, 2^27 input elements: P = 2 / 4 / 8 / 16
+// 4-bit reductions is vector instructions: 3 per element and peer that way,
+// against 29 available per element at HBM rate with 8 peers; this takes 2.1
+// (re-quantizing with 8 peers takes 2.9 per input element all told by the
+// counters, which keep the vector units 76 % busy).  In the kernels of the time,
+// which looped over tiles, 4 to 4 bits, 2^27 input elements: P = 2 / 4 / 8 / 16
 // 26.4 / 20.5 / 18.5 / 20.6 us -> 24.3 / 18.4 / 17.1 / 18.4.
 typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 

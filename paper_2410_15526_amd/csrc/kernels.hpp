@@ -830,8 +830,9 @@ constexpr int64_t kSpill = int64_t(NB == 0 ? 25 : NB <= 64 ? 31 : NB <= 256 ? 33
 //   8 and more peers beyond that, from 6 M on: 8-wave blocks <= 3 (P = 8, 2^24 / 50.8M
 //     24.9 / 67.7, 4-wave <= 4 26.9 / 71.4; P = 16, 2^23 20.2 and 24.3; below, P = 16,
 //     2.7 M 9.6 and 4-wave 8.5, P = 11, 5 M 11.3 and 10.6).
-//   4 peers with chunks of 2^24 and more: 2-wave blocks <= 8 (2^25 / 45969408 / 2^26
-//     36.1 / 44.5 / 65.6, 4-wave <= 4 36.7 / 44.5 / 67.9).
+//   4 peers with chunks of 2^24 and more: 2-wave blocks <= 8, for power-of-two chunks
+//     (2^25 / 2^26 36.1 / 65.1, 4-wave <= 4 36.7 / 68.0; others the same either way: 44 M
+//     44.5, 96 M 95.4 and 93.5, 203M 191.2 and 190.5).
 //   The rest: 4-wave blocks, <= 4 from 4 peers on, <= 5 for 3.
 template <int BITS_IN, int NB>
 int reduce_to_f32(const PeerTable &peers, int P, int64_t n, int gs, float cn, float out_scale, float *out_f32,
