@@ -107,17 +107,25 @@ class HotPath:
         return ([self.c4[q * m // 2:(q + 1) * m // 2] for q in range(self.Q)],
                 [self.s4[q * m // g:(q + 1) * m // g] for q in range(self.Q)])
 
+    _OWN_CHUNKS = (intra_chunks, inter_chunks)
+
+    def _own(self, chunks):
+        """Whether ``chunks`` is one of the two methods above, of this object."""
+        return getattr(chunks, "__self__", None) is self and getattr(chunks, "__func__", None) in self._OWN_CHUNKS
+
     # The chunks as the launches take them: addresses where they are slices of plain buffers (slicing 16
     # chunk tensors takes longer than a small reduction runs), else what intra_chunks / inter_chunks give --
-    # a program that receives its chunks from other GPUs overrides these.
+    # a program that receives its chunks from other GPUs puts its own in their place.
     def _intra(self, bits):
-        M, own = self.M, getattr(self.intra_chunks, "__func__", None) is HotPath.intra_chunks
-        return (own and sdp4.chunk_addresses(self.c8, self.s8, self.P, M * bits // 8, M // self.group)
+        M = self.M
+        return (self._own(self.intra_chunks)
+                and sdp4.chunk_addresses(self.c8, self.s8, self.P, M * bits // 8, M // self.group)
                 or self.intra_chunks(bits))
 
     def _inter(self):
-        m, own = self.m, getattr(self.inter_chunks, "__func__", None) is HotPath.inter_chunks
-        return (own and sdp4.chunk_addresses(self.c4, self.s4, self.Q, m // 2, m // self.group)
+        m = self.m
+        return (self._own(self.inter_chunks)
+                and sdp4.chunk_addresses(self.c4, self.s4, self.Q, m // 2, m // self.group)
                 or self.inter_chunks())
 
     def reduce_intra(self, stream=None, bits_in=8):

@@ -50,3 +50,19 @@ def test_chunks_set_on_an_object_are_used(calls):
     h.inter_chunks = lambda: ("c4", "s4")
     reductions(h)
     assert calls == [("c8", "s8"), ("c4", "s4"), ("c8", "s8")]
+
+
+def test_chunks_of_another_object_are_used(calls):
+    """Bound methods of another HotPath, whose message is the one to reduce."""
+    h, other = make(HotPath), make(HotPath)
+    h.intra_chunks, h.inter_chunks = other.intra_chunks, other.inter_chunks
+    reductions(h)
+    buffers = [other.c8, other.c4, other.c8]
+    assert [c[0][0].data_ptr() for c in calls] == [b.data_ptr() for b in buffers]
+
+
+def test_chunks_patched_into_the_class_are_used(calls, monkeypatch):
+    monkeypatch.setattr(HotPath, "intra_chunks", lambda self, bits=8: ("c8", "s8"))
+    monkeypatch.setattr(HotPath, "inter_chunks", lambda self: ("c4", "s4"))
+    reductions(make(HotPath))
+    assert calls == [("c8", "s8"), ("c4", "s4"), ("c8", "s8")]
