@@ -92,8 +92,9 @@ def _bind(L) -> None:
     except ImportError as e:
         warnings.warn(f"sdp4: no native argument marshalling, calls take longer on the host: {e}", RuntimeWarning)
         return
-    if _binding.torch_version != torch.__version__:
-        warnings.warn(f"sdp4: native argument marshalling was built for torch {_binding.torch_version}, not "
+    built_for = getattr(_binding, "torch_version", None)  # None: built before it was recorded
+    if built_for != torch.__version__:
+        warnings.warn(f"sdp4: native argument marshalling was built for torch {built_for}, not "
                       f"{torch.__version__}, and is not used: calls take longer on the host", RuntimeWarning)
         return
     _binding.bind(*[C.cast(getattr(L, "sdp4_" + n), C.c_void_p).value for n in

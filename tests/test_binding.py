@@ -58,6 +58,16 @@ def test_binding_of_another_torch_is_not_used(monkeypatch):
 
 
 @pytest.mark.cpu_only
+def test_binding_that_does_not_name_its_torch_is_not_used(monkeypatch):
+    """One built from sources that recorded no version."""
+    f = native()
+    _unbound(monkeypatch)
+    monkeypatch.delattr(f, "torch_version")
+    with pytest.warns(RuntimeWarning, match="built for torch None"):
+        _takes_the_general_path()
+
+
+@pytest.mark.cpu_only
 def test_leaves_what_is_not_on_a_gpu_or_not_ordinary():
     f = native()
     t = lambda n, dt=torch.float32: torch.zeros(n, dtype=dt)  # noqa: E731
