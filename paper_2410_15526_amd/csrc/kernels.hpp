@@ -360,13 +360,13 @@ __global__ __launch_bounds__(kWave * WPB) void k_qwd_decode(
         constexpr int per = BF16 ? 8 : 4;
         const uint32_t rem = at.in_group(gs);
         const uint32_t gi = (at.wave * Pl::W + E * at.lane + rem) >> gs;
+        load_chunks<WHOLE>(wb, at.wave, at.lane, valid / per, tw); // first: the transposition waits for them alone
         if (WHOLE || (int)(E * at.lane) < valid) {
             load_words<CWD>(reinterpret_cast<const char *>(codes + at.base / 2) + (at.wave * kWave + at.lane) * (CWD * 4u), cw);
             s = load_header(scale + (at.base >> gs), gi);
             if constexpr (!SYM)
                 mn = load_header(minv + (at.base >> gs), gi);
         }
-        load_chunks<WHOLE>(wb, at.wave, at.lane, valid / per, tw);
         float w[E];
         u32x4 c[RP];
         transpose_in<RP>(tw, lds, c, at.lane);
