@@ -726,8 +726,9 @@ struct Requant {
 // 2 to 7 peers then 16 per lane in 4-wave blocks <= 6, for 2 uncapped (P = 4, 11 M 15.3,
 // 32 per lane 15.9; P = 6, 12 M 18.1 and 20.3; P = 2, 12 M 12.45, <= 6 13.9) and from 16 M on in 8-wave blocks <= 3 (P = 2 / 4,
 // 128 M 114.8 / 138.5, 4-wave 116.5 / 141, 32 per lane 131.9 / 155.9; 1 peer 114.7, 32
-// per lane 110.5).  8-bit messages of 16 peers and 4 M or more: 8-wave blocks <= 3
-// (8 / 16 M 34.2 / 66.6, 4-wave 36.6 / 71.7).
+// per lane 110.5).  8-bit messages of 16 peers from 4.75 M on: 8-wave blocks <= 3
+// (chunks of 5 / 6 / 8 / 16 M 21.8 / 24.8 / 35.6 / 67.5, 4-wave 22.3 / 26.3 / 38.0 /
+// 72.5; sizes between within 2 % either way; 4 to 4.6 M 21.9 and 20.0).
 //
 // Stochastic rounding takes the same shapes.  Its kernels are bound by instructions,
 // and a cap does not move them (8 to 4 bits, as here and uncapped: P = 2, 128 M 68.7
@@ -776,7 +777,7 @@ int requant_for(const PeerTable &peers, int P, int64_t n, int gs, uint8_t *out_c
             return P < 8 ? go(Shape<32, 4, peer_range(1, 7)>{}, 6, f32) : go(Shape<16, 8, peer_range(8, 16)>{}, 4, f32);
         } else {
             const bool large = n >= 64 * M, small = n < 8 * M;
-            if (P & (P - 1) || (P == 8 && !small) || (P == 4 && !small && !large) || (F32 && P == 16 && n >= 4 * M))
+            if (P & (P - 1) || (P == 8 && !small) || (P == 4 && !small && !large) || (F32 && P == 16 && n >= 19 * M / 4))
                 return go(Shape<16, 8, F32 ? peer_range(3, 16) : peer_range(3, 15)>{}, P == 8 && large ? 2 : 3, f32);
             return go(Shape<16, 4, (1u << 1 | 1u << 2 | 1u << 4 | 1u << 8 | 1u << 16)>{}, P >= 4 ? 4 : 8, f32);
         }

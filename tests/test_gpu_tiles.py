@@ -251,7 +251,8 @@ M = 1 << 20
 @pytest.mark.parametrize("bits_in,P,n", [(4, 1, 4 * M), (4, 3, 4 * M + 8192), (4, 4, 9 * M - 4096), (4, 4, 9 * M),
                                          (4, 7, 16 * M - 4096), (4, 2, 16 * M), (4, 8, 4 * M), (4, 8, 4 * M + 4096),
                                          (4, 8, 9 * M), (4, 11, 4 * M + 4096), (4, 16, 4 * M), (8, 16, 4 * M - 4096),
-                                         (8, 16, 4 * M), (8, 11, 4 * M + 4096), (8, 5, 12288), (8, 8, 8 * M + 4096)])
+                                         (8, 16, 4 * M), (8, 16, 19 * M // 4 - 8192),
+                                         (8, 16, 19 * M // 4 - 4096), (8, 11, 4 * M + 4096), (8, 5, 12288), (8, 8, 8 * M + 4096)])
 @pytest.mark.parametrize("group", [32, 4096])
 def test_large_requant_with_and_without_the_float32_copy(bits_in, P, n, group):
     n += group
