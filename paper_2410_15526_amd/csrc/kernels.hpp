@@ -824,8 +824,10 @@ constexpr int64_t kSpill = int64_t(NB == 0 ? 25 : NB <= 64 ? 31 : NB <= 256 ? 33
 //     transform: P = 2, 8 M 8.4 and 7.1; P = 4, 5.5 M 8.05 and 5.96; P = 6, 4.5 M 8.0
 //     and 6.3; P = 8, 4 M 7.9 and 6.6; 256 points: P = 5, 5.5 M 8.5 and 7.1; below
 //     kSpill, 256 points, P = 4, 3.5 M 5.1 and 5.5; P = 4, 2^27 124 and 133).  9 to 15
-//     peers the same from 5 M, with a transform 6.5 M, to 9 M (P = 11, 7 M, no transform
-//     / 256 points 14.4 / 15.3, 8-wave blocks 15.8 / 15.8).  While the result is of the
+//     peers the same from 5 M, with a transform 9 to 11 from 6.5 M, to 9 M (P = 11, 7 M,
+//     no transform / 256 points 14.4 / 15.3, 8-wave blocks 15.8 / 15.8; 8 M with a
+//     transform P = 9 / 11 / 12 / 13 16.0 / 18.1 / 20.6 / 21.9 and 17.6 / 18.5 / 19.3 / 19.7).
+//     While the result is of the
 //     order of the L2s, 6.5 to 8 M, from 4 peers on without a transform in the guarded
 //     form (P = 4, 7.5 M 8.2, exact 9.2; P = 7, 7 M 9.5 and 12.0, 9 M 14.6 and 14.7).
 //   8 and more peers beyond that, from 6 M on: 8-wave blocks <= 3 (P = 8, 2^24 / 50.8M
@@ -856,7 +858,7 @@ int reduce_to_f32(const PeerTable &peers, int P, int64_t n, int gs, float cn, fl
     const int64_t bytes = n * (8 * 4 + P * BITS_IN) / 8;
     if constexpr (BITS_IN == 4) {
         const int64_t from = kSpill<NB> + (P == 2 ? 11 * M : P == 3 ? 5 * M : 0);
-        if (P >= (NB == 0 ? 2 : 3) && (P <= 8 ? bytes >= from : P < 16 && n > (NB == 0 ? 5 * M : 13 * M / 2))) {
+        if (P >= (NB == 0 ? 2 : 3) && (P <= 8 ? bytes >= from : P < (NB == 0 ? 16 : 12) && n > (NB == 0 ? 5 * M : 13 * M / 2))) {
             if constexpr (NB == 0) {
                 if (P >= 4 && P <= 8 && n >= 13 * M / 2 && n <= 8 * M)
                     return go(Shape<32, 4, peer_range(4, 8)>{}, 4, guarded);

@@ -289,7 +289,7 @@ F32_4_BIT = [(0, 4, 4368896), (0, 4, 4369152), (0, 4, 13 * M // 2 - 256), (0, 4,
              (0, 16, 6 * M - 256), (0, 16, 6 * M), (0, 2, 20 * M), (0, 1, 20 * M + 256), (32, 5, 5000960), (32, 5, 5001216),
              (0, 2, 36 * M // 5), (0, 2, 36 * M // 5 + 256), (0, 2, 12 * M), (64, 6, 6 * M), (256, 7, 4613632), (256, 7, 4613888), (256, 4, 12 * M - 256), (256, 4, 12 * M),
              (256, 4, 16 * M - 256), (256, 4, 16 * M), (256, 8, 13 * M // 2 - 256), (256, 8, 13 * M // 2),
-             (256, 11, 13 * M // 2 + 256), (2, 4, 7 * M), (512, 6, 6 * M), (1024, 6, 5691392), (1024, 6, 5692416),
+             (256, 11, 13 * M // 2 + 256), (256, 12, 7 * M), (2, 4, 7 * M), (512, 6, 6 * M), (1024, 6, 5691392), (1024, 6, 5692416),
              (1024, 1, 11 * M), (1024, 8, 7 * M), (512, 8, 9 * M)]
 F32_8_BIT = [(0, 4, 25 * M // 8 - 256), (0, 4, 25 * M // 8), (0, 4, 49 * M // 8), (0, 4, 49 * M // 8 + 256), (0, 3, 5392896),
              (0, 3, 5393152), (0, 8, 4 * M), (0, 8, 4 * M + 256), (256, 5, 4 * M), (1024, 5, 38 * M // 8), (32, 6, 13 * M // 4)]
