@@ -830,9 +830,10 @@ constexpr int64_t kSpill = int64_t(NB == 0 ? 25 : NB <= 64 ? 31 : NB <= 256 ? 33
 //     While the result is of the
 //     order of the L2s, 6.5 to 8 M, from 4 peers on without a transform in the guarded
 //     form (P = 4, 7.5 M 8.2, exact 9.2; P = 7, 7 M 9.5 and 12.0, 9 M 14.6 and 14.7).
-//   8 and more peers beyond that, from 6 M on: 8-wave blocks <= 3 (P = 8, 2^24 / 50.8M
-//     24.9 / 67.7, 4-wave <= 4 26.9 / 71.4; P = 16, 2^23 20.2 and 24.3; below, P = 16,
-//     2.7 M 9.6 and 4-wave 8.5, P = 11, 5 M 11.3 and 10.6).
+//   8 and more peers beyond that, above 5 M: 8-wave blocks <= 3 (P = 8, 2^24 / 50.8M
+//     24.9 / 67.7, 4-wave <= 4 26.9 / 71.4; P = 16, 2^23 20.2 and 24.3; with a transform,
+//     P = 9 / 11 / 13 / 16, 5.05 to 5.5 M 11.7 / 13.0 / 14.1 / 15.5, 4-wave 12.2 / 13.8 / 15.3
+//     / 16.1, 4.6 to 5 M 11.7 / 12.8 / 14.0 / 15.1 and 10.9 / 12.1 / 13.2 / 14.3).
 //   4 peers with chunks of 2^24 and more: 2-wave blocks <= 8, for power-of-two chunks
 //     (2^25 / 2^26 36.1 / 65.1, 4-wave <= 4 36.7 / 68.0; others the same either way: 44 M
 //     44.5, 96 M 95.4 and 93.5, 203M 191.2 and 190.5).
@@ -866,7 +867,7 @@ int reduce_to_f32(const PeerTable &peers, int P, int64_t n, int gs, float cn, fl
             if (P <= 4 ? n < 12 * M : P < 8 || (P == 8 ? n < (NB > 256 ? 9 * M : 13 * M / 2) : n <= 9 * M))
                 return go(Shape<32, 4, peer_range(NB == 0 ? 2 : 3, 15)>{}, 4, exact);
         }
-        if (P >= 8 && n >= 6 * M)
+        if (P >= 8 && n > 5 * M)
             return go(Shape<16, 8, peer_range(8, 16)>{}, 3, exact);
         if (P == 4 && n >= 16 * M)
             return go(Shape<16, 2, 1u << 4>{}, 8, exact);

@@ -286,6 +286,7 @@ def test_large_requant_with_and_without_the_float32_copy(bits_in, P, n, group):
 F32_4_BIT = [(0, 4, 4368896), (0, 4, 4369152), (0, 4, 13 * M // 2 - 256), (0, 4, 13 * M // 2), (0, 7, 8 * M),
              (0, 7, 8 * M + 256), (0, 8, 25 * M // 8 - 256), (0, 8, 25 * M // 8), (0, 8, 13 * M // 2), (0, 8, 8 * M + 256),
              (0, 3, 5719552), (0, 3, 5719808), (0, 3, 12 * M), (0, 11, 5 * M), (0, 11, 5 * M + 256), (0, 9, 9 * M + 256),
+             (0, 16, 5 * M), (0, 16, 5 * M + 256), (256, 11, 5 * M), (256, 11, 5 * M + 256),
              (0, 16, 6 * M - 256), (0, 16, 6 * M), (0, 2, 20 * M), (0, 1, 20 * M + 256), (32, 5, 5000960), (32, 5, 5001216),
              (0, 2, 36 * M // 5), (0, 2, 36 * M // 5 + 256), (0, 2, 12 * M), (64, 6, 6 * M), (256, 7, 4613632), (256, 7, 4613888), (256, 4, 12 * M - 256), (256, 4, 12 * M),
              (256, 4, 16 * M - 256), (256, 4, 16 * M), (256, 8, 13 * M // 2 - 256), (256, 8, 13 * M // 2),
