@@ -17,8 +17,9 @@ int qwd_encode(const float *w_new, const void *w_prev, bool sym, int64_t n, int 
 
 // 2-wave blocks, <= 8 per CU, 16 elements per lane for bfloat16 weights and 8 for float32: 2 KiB of weights
 // read and written per wave (2^30 elements, <= 6 / 8 / 10 per CU: bfloat16 826 / 751 / 759 us, float32 <= 6 / 7 /
-// 8 / 10 1526 / 1440 / 1408 / 1419).  Uncapped up to 2^23 elements (uncapped / <= 8: bfloat16, 5.7M 5.4 / 6.0, 7.3M
-// 7.0 / 7.1, 2^24 13.7 / 13.7; float32, 2.9M 5.0 / 5.4, 7.3M 11.3 / 11.6, 2^25 45.4 / 45.5).
+// 8 / 10 1526 / 1440 / 1408 / 1419).  Uncapped up to 2^23 elements (uncapped / <= 8, new inputs
+// each pass: bfloat16, 5.8M 6.9 / 7.0, 7.3M 8.2 / 8.4, 2^24 14.7 / 14.8; float32, 2.9M 6.25 / 6.25, 7.3M 12.6 / 12.8,
+// 2^25 46.7 / 46.9).
 template <bool BF16>
 int qwd_decode(const uint8_t *codes, const float *scale, const float *minv, int64_t n, int gs, void *w_prev, bool sym,
                hipStream_t s)
