@@ -107,26 +107,19 @@ class HotPath:
         return ([self.c4[q * m // 2:(q + 1) * m // 2] for q in range(self.Q)],
                 [self.s4[q * m // g:(q + 1) * m // g] for q in range(self.Q)])
 
-    _OWN_CHUNKS = (intra_chunks, inter_chunks)
-
-    def _own(self, chunks):
-        """Whether ``chunks`` is one of the two methods above, of this object."""
-        return getattr(chunks, "__self__", None) is self and getattr(chunks, "__func__", None) in self._OWN_CHUNKS
-
     # The chunks as the launches take them: addresses where they are slices of plain buffers (slicing 16
     # chunk tensors takes longer than a small reduction runs), else what intra_chunks / inter_chunks give --
-    # a program that receives its chunks from other GPUs puts its own in their place.
+    # a program that receives its chunks from other GPUs puts its own in their place, in a subclass, in the
+    # class or on the object.
     def _intra(self, bits):
-        M = self.M
-        return (self._own(self.intra_chunks)
-                and sdp4.chunk_addresses(self.c8, self.s8, self.P, M * bits // 8, M // self.group)
-                or self.intra_chunks(bits))
+        M, chunks = self.M, self.intra_chunks
+        own = getattr(chunks, "__func__", None) is _INTRA_CHUNKS and chunks.__self__ is self
+        return own and sdp4.chunk_addresses(self.c8, self.s8, self.P, M * bits // 8, M // self.group) or chunks(bits)
 
     def _inter(self):
-        m = self.m
-        return (self._own(self.inter_chunks)
-                and sdp4.chunk_addresses(self.c4, self.s4, self.Q, m // 2, m // self.group)
-                or self.inter_chunks())
+        m, chunks = self.m, self.inter_chunks
+        own = getattr(chunks, "__func__", None) is _INTER_CHUNKS and chunks.__self__ is self
+        return own and sdp4.chunk_addresses(self.c4, self.s4, self.Q, m // 2, m // self.group) or chunks()
 
     def reduce_intra(self, stream=None, bits_in=8):
         c, s = self._intra(bits_in)
@@ -232,3 +225,7 @@ class HotPath:
                                      u["d2"][q * m:(q + 1) * m], stream=stream)
         sdp4.sdp4_reduce_f32([u["d2"][q * m:(q + 1) * m] for q in range(Q)], u["r2"], stream=stream)
         sdp4.sdp4_hadamard(u["r2"], self.out, self.block, stream=stream)
+
+
+# HotPath's own, as the class defines them
+_INTRA_CHUNKS, _INTER_CHUNKS = HotPath.intra_chunks, HotPath.inter_chunks
