@@ -112,14 +112,14 @@ class HotPath:
     # a program that receives its chunks from other GPUs puts its own in their place, in a subclass, in the
     # class or on the object.
     def _intra(self, bits):
-        M, chunks = self.M, self.intra_chunks
-        own = getattr(chunks, "__func__", None) is _INTRA_CHUNKS and chunks.__self__ is self
-        return own and sdp4.chunk_addresses(self.c8, self.s8, self.P, M * bits // 8, M // self.group) or chunks(bits)
+        M, own = self.M, type(self).intra_chunks is _INTRA_CHUNKS and "intra_chunks" not in self.__dict__
+        return (own and sdp4.chunk_addresses(self.c8, self.s8, self.P, M * bits // 8, M // self.group)
+                or self.intra_chunks(bits))
 
     def _inter(self):
-        m, chunks = self.m, self.inter_chunks
-        own = getattr(chunks, "__func__", None) is _INTER_CHUNKS and chunks.__self__ is self
-        return own and sdp4.chunk_addresses(self.c4, self.s4, self.Q, m // 2, m // self.group) or chunks()
+        m, own = self.m, type(self).inter_chunks is _INTER_CHUNKS and "inter_chunks" not in self.__dict__
+        return (own and sdp4.chunk_addresses(self.c4, self.s4, self.Q, m // 2, m // self.group)
+                or self.inter_chunks())
 
     def reduce_intra(self, stream=None, bits_in=8):
         c, s = self._intra(bits_in)
